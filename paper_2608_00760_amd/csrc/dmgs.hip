@@ -963,21 +963,32 @@ int post_pass(dmgs_plan P, int k, T** cur, T** other, const T* ec, const T* q, i
     return sweeps<T>(P, k, *cur, q, nu_post_of(P, order), order, st);
 }
 
+// Levels k .. L-1 of the plan as cells per axis, for small_fits.
+int small_counts(dmgs_plan P, int k, int (*nc)[3]) {
+    const int nl = P->L - k;
+    if (nl > kSmallMaxLevels) return 0;
+    for (int i = 0; i < nl; i++)
+        for (int a = 0; a < 3; a++) nc[i][a] = P->lev[k + i].nc[a];
+    return nl;
+}
+
 template <class T, bool HARM>
 int launch_small_t(dmgs_plan P, int k, const T* q, T* u, int order, hipStream_t st) {
     SmallArgs<T> a;
-    int Ns[kSmallMaxLevels];
-    a.nlev = P->L - k;
-    int off = 0;
+    int nc[kSmallMaxLevels][3];
+    a.nlev = small_counts(P, k, nc);
+    if (!small_fits(nc, a.nlev)) {
+        set_error("internal: levels from %d do not fit the coarse kernel", k);
+        return DMGS_ERR_INVALID;
+    }
     for (int i = 0; i < a.nlev; i++) {
         const Level& l = P->lev[k + i];
-        a.lev[i].N = Ns[i] = l.N;
-        a.lev[i].nv = (int)l.nv;
-        a.lev[i].off = off;
-        off += 4 * (int)l.nv;
+        for (int x = 0; x < 3; x++) {
+            a.lev[i].nc[x] = nc[i][x];
+            a.lev[i].s[x] = (T)((HARM ? 2.0 : 0.5) / (l.h3[x] * l.h3[x]));
+        }
         a.lev[i].D = Typed<T>::D(l);
-        a.lev[i].w = Typed<T>::w(l);
-        a.lev[i].st = l.stencil<T>(HARM);
+        a.lev[i].w = P->grid ? Typed<T>::mu(l) : Typed<T>::w(l);
     }
     a.q = q;
     a.u = u;
@@ -985,11 +996,10 @@ int launch_small_t(dmgs_plan P, int k, const T* q, T* u, int order, hipStream_t 
     a.nu_pre = nu_pre_of(P, order);
     a.nu_post = nu_post_of(P, order);
     a.order = order;
-    a.roff = off;
-    size_t bytes = small_lds_bytes<T>(Ns, a.nlev);
+    a.from_mu = P->grid ? 1 : 0;
     const void* grp = nullptr;
     if constexpr (sizeof(T) == 4) grp = (const void*)k_small_grp<T, HARM>;
-    return launch_rec(P, (const void*)k_small_vcycle<T, HARM>, grp, 1u, kSmallThreads, bytes, a, st);
+    return launch_rec(P, (const void*)k_small_vcycle<T, HARM>, grp, 1u, kSmallThreads, small_lds_bytes<T>(), a, st);
 }
 
 template <class T>
@@ -2288,12 +2298,14 @@ int kernel_attributes(int device) {
     static bool done[kDevices] = {};
     std::lock_guard<std::mutex> guard(lock);
     if (device >= 0 && device < kDevices && done[device]) return DMGS_OK;
-    const int lim = (int)kSmallLdsLimit;
-    const void* fns[] = {(const void*)k_small_vcycle<float, false>, (const void*)k_small_vcycle<float, true>,
-                         (const void*)k_small_vcycle<double, false>, (const void*)k_small_vcycle<double, true>,
-                         (const void*)k_small_grp<float, false>, (const void*)k_small_grp<float, true>};
-    for (const void* f : fns)
-        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) != hipSuccess) {
+    const int lim32 = (int)small_lds_bytes<float>(), lim64 = (int)small_lds_bytes<double>();
+    static_assert(small_lds_bytes<double>() <= 160 * 1024, "the coarse kernel's levels exceed the LDS");
+    const std::pair<const void*, int> fns[] = {
+        {(const void*)k_small_vcycle<float, false>, lim32}, {(const void*)k_small_vcycle<float, true>, lim32},
+        {(const void*)k_small_vcycle<double, false>, lim64}, {(const void*)k_small_vcycle<double, true>, lim64},
+        {(const void*)k_small_grp<float, false>, lim32}, {(const void*)k_small_grp<float, true>, lim32}};
+    for (const auto& f : fns)
+        if (hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, f.second) != hipSuccess) {
             (void)hipGetLastError(); set_error("hipFuncSetAttribute failed");
             return DMGS_ERR_HIP;
         }
@@ -2414,6 +2426,10 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
         Level& l = P->lev[k];
         l.N = N;
         l.n = N + 1;
+        for (int a = 0; a < 3; a++) {
+            l.nc[a] = N;
+            l.h3[a] = h;
+        }
         l.nv = s.nv[k];
         l.h = h;
         l.inv_h2 = 1.0 / (h * h);
@@ -2492,8 +2508,7 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     }
     P->cfg_sweep = 0;
     P->cfg_fuse_min = kn.fuse_min;
-    // first level handled by the single-workgroup kernel (N <= 16 in float32,
-    // N <= 8 in float64, all remaining levels within the LDS budget)
+    // first level handled by the single-workgroup kernel (at most 16 cells per axis)
     P->small32 = P->small64 = -1;
     P->small2 = -1;
     int small2_max = kSmall2MaxN;
@@ -2504,12 +2519,12 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
             break;
         }
     for (int k = 1; k < P->L && st == DMGS_OK && o->ndim != 2; k++) {
-        int Ns[kSmallMaxLevels];
-        int nl = P->L - k;
-        if (nl > kSmallMaxLevels) continue;
-        for (int i = 0; i < nl; i++) Ns[i] = P->lev[k + i].N;
-        if (P->small32 < 0 && P->lev[k].N <= 16 && small_lds_bytes<float>(Ns, nl) <= kSmallLdsLimit) P->small32 = k;
-        if (P->small64 < 0 && P->lev[k].N <= 8 && small_lds_bytes<double>(Ns, nl) <= kSmallLdsLimit) P->small64 = k;
+        int nc[kSmallMaxLevels][3];
+        const int nl = small_counts(P, k, nc);
+        if (small_fits(nc, nl)) {
+            P->small32 = P->small64 = k;
+            break;
+        }
     }
     if (st == DMGS_OK) st = kernel_attributes(P->device);
     P->cfg_block_max = kn.block_max;
