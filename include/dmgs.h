@@ -175,11 +175,13 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options *opt);
  *   DMGS_FUSE_MIN (32 / 16)     smallest N of the fused passes (float32 / float64 plans)
  *   DMGS_BLOCK_MAX (64)         largest N of the LDS block passes
  *   DMGS_DR_WGS (512 / 1024)    target workgroups of the defect-restriction pass (float32 / float64 plans)
- *   DMGS_2D_SWEEP2_MIN (1536)   two-dimensional plans: smallest N of the two-sweep passes
- *   DMGS_2D_BLOCK_MIN (64)      ... smallest N of the LDS block passes
+ *   DMGS_2D_SWEEP2_MIN          two-dimensional plans: smallest N of the row-marching two-sweep
+ *                               passes (unset: none in V(2,2) plans, whose levels run the block
+ *                               passes, 1536 in others)
+ *   DMGS_2D_BLOCK_MIN (4)       ... smallest N of the block passes
  *   DMGS_2D_DEFECT (1)          ... the last pre-smoothing pass writes the defect
  *   DMGS_2D_CHUNK (0)           ... rows per chunk of the two-sweep passes (0: from the grid size)
- *   DMGS_2D_SMALL_MAX (32)      ... largest N of the single-workgroup coarse kernel
+ *   DMGS_2D_SMALL_MAX (64)      ... largest N of the single-workgroup coarse kernel
  *   DMGS_EPI_FUSE (1)           dmgs_likelihood_grad computes its epilogue in the
  *                               forward solve's last refinement step (0: separate pass)
  *   DMGS_PAD (1)                refinement plans pad the rows of the finest level's

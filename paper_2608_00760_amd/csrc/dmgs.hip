@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <climits>
 #include <cstring>
 #include <cstdlib>
 #include <algorithm>
@@ -1277,6 +1278,29 @@ int sweeps2(dmgs_plan P, int k, double** cur, double** other, const double* q, i
     return DMGS_OK;
 }
 
+// One smoothing phase of level k in register blocks (k2_block_pass): mode 0 /
+// 1 pre-smoothing from u_in / from zero with the restricted defect in qc, 2
+// post-smoothing of u_in + I ec.
+template <bool HARM, int MODE>
+int launch_block2(dmgs_plan P, int k, const double* u_in, double* u_out, const double* q, const double* ec, double* qc,
+                  int first, hipStream_t st) {
+    const Level& l = P->lev[k];
+    const int nt = (l.N + block2_tile(MODE) - 1) / block2_tile(MODE);
+    const double coarse = 8.0 * P->lev[k + 1].nv;
+    TIMED(P, k, DMGS_K_SMOOTH, (MODE == 1 ? 32.0 : 40.0) * l.nv + coarse, st,
+          hipLaunchKernelGGL((k2_block_pass<HARM, MODE>), dim3(nt * nt), dim3(kB2Threads), 0, st, u_in, u_out, q,
+                             (const double*)l.D64, (const double*)l.mu64, ec, qc, l.N, l.stencil<double>(HARM), first, nt));
+    return DMGS_OK;
+}
+
+template <bool HARM>
+int block_pass2(dmgs_plan P, int k, const double* u_in, double* u_out, const double* q, const double* ec, double* qc,
+                int mode, int first, hipStream_t st) {
+    if (mode == 2) return launch_block2<HARM, 2>(P, k, u_in, u_out, q, ec, qc, first, st);
+    if (mode == 1) return launch_block2<HARM, 1>(P, k, u_in, u_out, q, ec, qc, first, st);
+    return launch_block2<HARM, 0>(P, k, u_in, u_out, q, ec, qc, first, st);
+}
+
 // One V-cycle on level k of a two-dimensional plan with iterate *cur (from 0
 // when zero; the level's other buffer is *other, whose boundary holds the
 // same values); order 1 is the transposed cycle.  On return *cur holds the
@@ -1300,39 +1324,23 @@ int vcycle2(dmgs_plan P, int k, double** cur, double** other, const double* q, i
         a.nu_pre = nu_pre_of(P, order);
         a.nu_post = nu_post_of(P, order);
         a.first = order ? 1 : 0;
-        const size_t lds = (size_t)small2_words(a.N, a.nl) * sizeof(double);
-        hipLaunchKernelGGL(k2_small_vcycle<HARM>, dim3(1), dim3(1024), lds, st, a);
+        a.cinv = P->cinv;
+        hipLaunchKernelGGL(k2_small_vcycle<HARM>, dim3(1), dim3(1024), kSmall2Lds, st, a);
         LAUNCHCHK();
         return DMGS_OK;
     }
     const int first = order ? 1 : 0;
-    // block passes run two workgroups per CU: take them where the tiles fill
-    // whole rounds (a nearly empty last round costs more than they save)
-    const int btiles = ((l.N + kB2 - 1) / kB2) * ((l.N + kB2 - 1) / kB2);
-    const bool bfits = btiles <= 2 * P->ncu || btiles % (2 * P->ncu) == 0;
-    if (k < P->L - 1 && l.N >= P->cfg_2d_block_min && l.N < P->cfg_2d_sweep2_min && bfits && nu_pre_of(P, order) == 2 &&
+    if (k < P->L - 1 && l.N >= P->cfg_2d_block_min && l.N < P->cfg_2d_sweep2_min && nu_pre_of(P, order) == 2 &&
         nu_post_of(P, order) == 2) {
         // mid-size level: each smoothing phase in one launch of LDS tiles,
         // the defect restricted by the pre-smoothing one
         const Level& c = P->lev[k + 1];
-        const int ntx = (l.N + kB2 - 1) / kB2;
-        const dim3 grid(ntx * ntx), block(256);
-        const Stencil<double> s = l.stencil<double>(HARM);
-        TIMED(P, k, DMGS_K_SMOOTH, (zero ? 32.0 : 40.0) * l.nv + 8.0 * c.nv, st,
-              if (zero) hipLaunchKernelGGL((k2_block_pass<HARM, 1>), grid, block, 0, st, (const double*)*cur, *other,
-                                           q, (const double*)l.D64, (const double*)l.mu64, (const double*)nullptr,
-                                           c.q64, l.N, s, first, ntx);
-              else hipLaunchKernelGGL((k2_block_pass<HARM, 0>), grid, block, 0, st, (const double*)*cur, *other, q,
-                                      (const double*)l.D64, (const double*)l.mu64, (const double*)nullptr, c.q64, l.N,
-                                      s, first, ntx));
+        TRY(block_pass2<HARM>(P, k, *cur, *other, q, nullptr, c.q64, zero ? 1 : 0, first, st));
         std::swap(*cur, *other);
         double* ccur = c.u64;
         double* coth = c.t64;
         TRY(vcycle2<HARM>(P, k + 1, &ccur, &coth, c.q64, order, true, st));
-        TIMED(P, k, DMGS_K_SMOOTH, 40.0 * l.nv + 8.0 * c.nv, st,
-              hipLaunchKernelGGL((k2_block_pass<HARM, 2>), grid, block, 0, st, (const double*)*cur, *other, q,
-                                 (const double*)l.D64, (const double*)l.mu64, (const double*)ccur, (double*)nullptr,
-                                 l.N, s, first, ntx));
+        TRY(block_pass2<HARM>(P, k, *cur, *other, q, ccur, nullptr, 2, first, st));
         std::swap(*cur, *other);
         return DMGS_OK;
     }
@@ -1994,7 +2002,15 @@ int build_hierarchy(dmgs_plan P, hipStream_t st, const double* logD = nullptr, c
                                (const double*)f.mu64, c.D64, c.mu64, f.N);
         LAUNCHCHK();
     }
-    if (!is2d(P)) {
+    if (is2d(P)) {
+        if (P->small2 >= 0) {
+            const Level& c = P->lev[P->L - 1];
+            const Stencil<double> s = c.stencil<double>(harmonic(P));
+            if (harmonic(P)) hipLaunchKernelGGL(k2_coarse_inverse<true>, dim3(1), dim3(64), 0, st, (const double*)c.D64, (const double*)c.mu64, c.N, s, P->cinv);
+            else hipLaunchKernelGGL(k2_coarse_inverse<false>, dim3(1), dim3(64), 0, st, (const double*)c.D64, (const double*)c.mu64, c.N, s, P->cinv);
+            LAUNCHCHK();
+        }
+    } else {
         const Level& c = P->lev[P->L - 1];
         hipLaunchKernelGGL(k_coarse_inverse, dim3(1), dim3(64), 0, st, (const double*)c.D64, (const double*)c.mu64, c.N,
                            c.stencil<double>(harmonic(P)), P->cinv);
@@ -2303,7 +2319,8 @@ int kernel_attributes(int device) {
     const std::pair<const void*, int> fns[] = {
         {(const void*)k_small_vcycle<float, false>, lim32}, {(const void*)k_small_vcycle<float, true>, lim32},
         {(const void*)k_small_vcycle<double, false>, lim64}, {(const void*)k_small_vcycle<double, true>, lim64},
-        {(const void*)k_small_grp<float, false>, lim32}, {(const void*)k_small_grp<float, true>, lim32}};
+        {(const void*)k_small_grp<float, false>, lim32}, {(const void*)k_small_grp<float, true>, lim32},
+        {(const void*)k2_small_vcycle<false>, (int)kSmall2Lds}, {(const void*)k2_small_vcycle<true>, (int)kSmall2Lds}};
     for (const auto& f : fns)
         if (hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, f.second) != hipSuccess) {
             (void)hipGetLastError(); set_error("hipFuncSetAttribute failed");
@@ -2542,6 +2559,10 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     P->cfg_sweep2_wgs_coarse = std::max(16, P->cfg_sweep2_wgs / 2);
     if (const char* e = std::getenv("DMGS_SWEEP2_WGS_COARSE")) P->cfg_sweep2_wgs_coarse = std::max(16, std::atoi(e));
     if (const char* e = std::getenv("DMGS_SWEEP_CFG")) P->cfg_sweep = std::min(2, std::max(0, std::atoi(e)));
+    // V(2,2) cycles run the block passes on every level (4096^2: 172 / 151 us a
+    // phase, the row-marching passes 242 / 192 us); other smoothing counts
+    // have no block pass
+    P->cfg_2d_sweep2_min = o->nu_pre == 2 && o->nu_post == 2 ? INT_MAX : 1536;
     if (const char* e = std::getenv("DMGS_2D_SWEEP2_MIN")) P->cfg_2d_sweep2_min = std::max(4, std::atoi(e));
     if (const char* e = std::getenv("DMGS_SWEEP2_FP64")) P->cfg_sweep2_fp64 = std::atoi(e) != 0;
     if (const char* e = std::getenv("DMGS_2D_BLOCK_MIN")) P->cfg_2d_block_min = std::max(4, std::atoi(e));

@@ -601,272 +601,486 @@ __global__ __launch_bounds__(256) void k2_defect_restrict_rows(const double* __r
 namespace dmgs {
 
 // ---------------------------------------------------------------------------
+// Blocks of 2 x 2 vertices in registers, shared by the two kernels below.
+//
+// A thread owns the block with even corner (2 bx, 2 by): quadrant o = 2 (x&1)
+// + (y&1).  Its iterate, right-hand side, inverse diagonal and 12 face
+// coefficients stay in registers for a whole smoothing phase, so an update
+// reads only the two neighbours in other blocks, from LDS, where the iterate
+// lies by quadrant (consecutive lanes read consecutive words).  A vertex's
+// colour is its quadrant's bit parity.  Vertices that must not change (grid
+// boundary, outside) have w = 0.
+struct Pair2 {   // two vertices along y, aligned as one
+    double a, b;
+};
+
+struct Block2 {
+    double u[4], q[4], w[4];
+    double cx[2], cy[2];     // faces inside the block: along x (by y bit), along y (by x bit)
+    double ox[4], oy[4];     // faces to the neighbouring blocks, by quadrant
+
+    // Face coefficients from the block's D (published at base[idx + o S])
+    // and the neighbours' in LDS, and w = 1 / (their sum + mua) where keep.
+    template <bool HARM, int S, int X>
+    __device__ __forceinline__ void coefs(const double* base, int idx, const double* D, const double* mu, const bool* keep,
+                                          const Stencil<double>& st) {
+        double nx[4], ny[4];
+#pragma unroll
+        for (int o = 0; o < 4; o++) {
+            nx[o] = base[idx + (o ^ 2) * S + ((o & 2) ? X : -X)];
+            ny[o] = base[idx + (o ^ 1) * S + ((o & 1) ? 1 : -1)];
+        }
+#pragma unroll
+        for (int o = 0; o < 4; o++) {
+            ox[o] = face<HARM>(D[o], nx[o], st);
+            oy[o] = face<HARM>(D[o], ny[o], st);
+            if (!(o & 2)) cx[o & 1] = face<HARM>(D[o], D[o ^ 2], st);
+            if (!(o & 1)) cy[o >> 1] = face<HARM>(D[o], D[o ^ 1], st);
+        }
+#pragma unroll
+        for (int o = 0; o < 4; o++) {
+            const double d = ((ox[o] + cx[o & 1]) + (oy[o] + cy[o >> 1])) + mu[o];
+            w[o] = keep[o] ? 1.0 / d : 0.0;
+        }
+    }
+    // q + sum_j c_ij u_j at the two quadrants of colour C
+    template <int C, int S, int X>
+    __device__ __forceinline__ void numer(const double* base, int idx, double* v) const {
+        double nx[4], ny[4];
+#pragma unroll
+        for (int o = 0; o < 4; o++)
+            if ((__builtin_popcount(o) & 1) == C) {
+                nx[o] = base[idx + (o ^ 2) * S + ((o & 2) ? X : -X)];
+                ny[o] = base[idx + (o ^ 1) * S + ((o & 1) ? 1 : -1)];
+            }
+        __builtin_amdgcn_sched_barrier(0);   // issue every read before the first is waited for
+#pragma unroll
+        for (int o = 0; o < 4; o++)
+            if ((__builtin_popcount(o) & 1) == C)
+                v[o] = ((q[o] + cx[o & 1] * u[o ^ 2]) + cy[o >> 1] * u[o ^ 1]) + (ox[o] * nx[o] + oy[o] * ny[o]);
+    }
+    // Gauss-Seidel update of colour C, published; vertices with w = 0 keep
+    // their value (FIXED) or become 0
+    template <int C, int S, int X, bool FIXED>
+    __device__ __forceinline__ void half(double* base, int idx) {
+        double v[4];
+        numer<C, S, X>(base, idx, v);
+#pragma unroll
+        for (int o = 0; o < 4; o++)
+            if ((__builtin_popcount(o) & 1) == C) {
+                const double t = v[o] * w[o];
+                u[o] = FIXED && w[o] == 0.0 ? u[o] : t;
+                base[idx + o * S] = u[o];
+            }
+    }
+    // after a sweep that ended with the other colour: residual of colour C
+    // (the other's is 0), 0 where w = 0; all four published
+    template <int C, int S, int X>
+    __device__ __forceinline__ void residual(const double* base, int idx, double* r) const {
+        numer<C, S, X>(base, idx, r);
+#pragma unroll
+        for (int o = 0; o < 4; o++)
+            r[o] = (__builtin_popcount(o) & 1) != C || w[o] == 0.0 ? 0.0 : r[o] - u[o] / w[o];
+    }
+    // full weighting to the block's corner of what all blocks published:
+    // quadrant o of this block and, where its bit is set, of the one before
+    template <int S, int X>
+    __device__ __forceinline__ static double restricted(const double* base, int idx) {
+        const double a0 = base[idx], a1 = base[idx + S], b1 = base[idx + S - 1], a2 = base[idx + 2 * S],
+                     b2 = base[idx + 2 * S - X], a3 = base[idx + 3 * S], b3 = base[idx + 3 * S - 1],
+                     c3 = base[idx + 3 * S - X], d3 = base[idx + 3 * S - X - 1];
+        return (4.0 * a0 + 2.0 * ((a1 + b1) + (a2 + b2)) + ((a3 + b3) + (c3 + d3))) * (1.0 / 16.0);
+    }
+};
+
+// ---------------------------------------------------------------------------
 // The coarse end of a two-dimensional V-cycle in one workgroup: levels
-// ks .. L-1 (N_ks <= kSmall2MaxN), every field LDS-resident.  The correction
-// of level ks starts from 0 with a zero boundary (a coarse correction), and
-// the same steps as the per-level kernels run in the same order: nu_pre
-// sweeps, defect and restriction, the next level, prolongation and
-// correction, nu_post sweeps; the coarsest level is solved exactly (one
-// thread, Cholesky).  Barriers separate the steps.
-constexpr int kSmall2MaxN = 32, kSmall2MaxLevels = 6;
+// ks .. L-1 (N_ks <= kSmall2MaxN).  The correction of level ks starts from 0
+// with a zero boundary (a coarse correction); nu_pre sweeps, defect and
+// restriction, the next level, prolongation and correction, nu_post sweeps;
+// the coarsest level is solved exactly.
+//
+// Bound by latency: a chain of about 100 dependent steps.  The first level
+// has at most 32 x 32 blocks, one per thread; the second's (at most 256)
+// belong to waves 0 .. 3 as well, every further level's (at most 64) to one
+// wave of its own, whose steps need no barrier.
+//
+// 64 cells: with all fields in LDS and one vertex of a colour per thread the
+// levels 32^2 .. 2^2 took 81 us a call and 64^2 two launches of 13 and 16 us.
+constexpr int kSmall2MaxN = 64, kSmall2MaxLevels = 6;
+
+// Inverse of the coarsest operator (N in {2, 3}: 1 or 4 unknowns, padded to
+// 4 with the identity), by Gauss-Jordan in one thread, once per coefficient
+// set.
+template <bool HARM>
+__global__ void k2_coarse_inverse(const double* __restrict__ D, const double* __restrict__ mu, int N, Stencil<double> st,
+                                  double* __restrict__ inv) {
+    if (threadIdx.x != 0) return;
+    const int n = N + 1, m1 = N - 1, m = m1 * m1;
+    double M[4][4], R[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            M[t][c] = t == c ? 1.0 : 0.0;
+            R[t][c] = t == c ? 1.0 : 0.0;
+        }
+        if (t < m) {
+            const int x = 1 + t / m1, y = 1 + t % m1, v = x * n + y;
+            const double cxm = face<HARM>(D[v], D[v - n], st), cxp = face<HARM>(D[v], D[v + n], st);
+            const double cym = face<HARM>(D[v], D[v - 1], st), cyp = face<HARM>(D[v], D[v + 1], st);
+            M[t][t] = mu[v] + ((cxm + cxp) + (cym + cyp));
+            if (m == 4) {   // unknowns (1,1), (1,2), (2,1), (2,2)
+                M[t][t ^ 2] = -((t & 2) ? cxm : cxp);
+                M[t][t ^ 1] = -((t & 1) ? cym : cyp);
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 4; p++) {
+        const double ip = 1.0 / M[p][p];
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            M[p][c] *= ip;
+            R[p][c] *= ip;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            if (t == p) continue;
+            const double f = M[t][p];
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                M[t][c] -= f * M[p][c];
+                R[t][c] -= f * R[p][c];
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 16; t++) inv[t] = R[t >> 2][t & 3];
+}
 
 struct Small2Args {
     const double* q;                          // right-hand side of level ks
-    double* u;                                // its correction (written on every vertex)
+    double* u;                                // its correction (interior written)
     const double* D[kSmall2MaxLevels];
     const double* mu[kSmall2MaxLevels];
     Stencil<double> st[kSmall2MaxLevels];
     int N[kSmall2MaxLevels];
     int nl;                                   // levels ks .. L-1
+    const double* cinv;                       // inverse of the coarsest operator (4 x 4, padded with the identity)
     int nu_pre, nu_post, first;               // first: colour of the first half-sweep
 };
 
-__host__ __device__ inline int small2_words(const int* Ns, int nl) {
-    int w = 0;
-    for (int i = 0; i < nl; i++) w += 4 * (Ns[i] + 1) * (Ns[i] + 1);
-    return w;
+// LDS: quadrant o of block (bx, by) at off + o kS2S + bx kS2X + by.  What
+// lies past a row's last block is on the boundary (an unused entry, or the
+// next row's first vertex), a row of zeros follows the last.  The coarser
+// levels share one more set of quadrants, each in a corner of it.
+constexpr int kS2X = 32, kS2S = kS2X * 33, kS2Words = 2 * 4 * kS2S;
+__host__ __device__ constexpr int small2_off(int level) {
+    return level == 0 ? 0 : 4 * kS2S + (level == 1 ? 0 : level == 2 ? 20 : level == 3 ? 10 * kS2X + 20 : level == 4 ? 16 * kS2X + 20 : 20 * kS2X + 20);
 }
+__device__ __forceinline__ int small2_at(int off, int x, int y) {
+    return off + (2 * (x & 1) + (y & 1)) * kS2S + (x >> 1) * kS2X + (y >> 1);
+}
+constexpr size_t kSmall2Lds = (kS2Words + 16) * sizeof(double);
 
 template <bool HARM>
 __global__ __launch_bounds__(1024) void k2_small_vcycle(Small2Args a) {
     extern __shared__ double lds2[];
-    // level i holds u, q, D, mua (each (N_i + 1)^2) from lds2 + 4 sum_{j<i} (N_j + 1)^2
-    auto lvl = [&](int i) __attribute__((always_inline)) {
-        int off = 0;
-        for (int j = 0; j < i; j++) off += 4 * (a.N[j] + 1) * (a.N[j] + 1);
-        return lds2 + off;
-    };
-    auto nvl = [&](int i) __attribute__((always_inline)) { return (a.N[i] + 1) * (a.N[i] + 1); };
-#define U(i) (lvl(i))
-#define Q(i) (lvl(i) + nvl(i))
-#define DD(i) (lvl(i) + 2 * nvl(i))
-#define M(i) (lvl(i) + 3 * nvl(i))
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int i = 0; i < a.nl; i++) {
-        const int nv = (a.N[i] + 1) * (a.N[i] + 1);
-        for (int v = tid; v < nv; v += nt) {
-            U(i)[v] = 0.0;
-            Q(i)[v] = i == 0 ? a.q[v] : 0.0;
-            DD(i)[v] = a.D[i][v];
-            M(i)[v] = a.mu[i][v];
-        }
+    double* const base = lds2;
+    double* const sinv = lds2 + kS2Words;    // inverse of the coarsest operator, at most 4 x 4
+    const int tid = threadIdx.x, L = a.nl, first = a.first;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // this thread's blocks: A of level 0, B of level lb
+    const int lb = wave < 4 ? 1 : wave - 2;
+    const int sb = lb == 1 ? 4 : lb == 2 ? 3 : lb == 3 ? 2 : 1;
+    const int ax = tid >> 5, ay = tid & 31;
+    const int bx = (lb == 1 ? tid : tid & 63) >> sb, by = tid & ((1 << sb) - 1);
+    const bool actA = ax < a.N[0] / 2 && ay < a.N[0] / 2;
+    const bool hasB = lb < L - 1;
+    const int lB = hasB ? lb : 0;
+    const bool actB = hasB && bx < a.N[lB] / 2 && by < a.N[lB] / 2;
+    const int idA = small2_off(0) + ax * kS2X + ay, idB = small2_off(lB) + (hasB ? bx * kS2X + by : 0);
+    Block2 A, B;
+    {
+        // D, mua and q of both blocks, and the D past the end of each axis
+        auto load = [&](const double* p, int N, int x, int y, bool on, double none, double* v) {
+#pragma unroll
+            for (int o = 0; o < 4; o += 2) {
+                const Pair2 t = on ? *reinterpret_cast<const Pair2*>(p + (2 * x + (o >> 1)) * (N + 1) + 2 * y) : Pair2{none, none};
+                v[o] = t.a;
+                v[o + 1] = t.b;
+            }
+        };
+        auto edges = [&](const double* p, int N, int x, int y, bool on, double* e) {
+            const int n = N + 1;
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                e[k] = on && x == N / 2 - 1 ? p[N * n + 2 * y + k] : 0.0;
+                e[2 + k] = on && y == N / 2 - 1 ? p[(2 * x + k) * n + N] : 0.0;
+            }
+        };
+        double DA[4], mA[4], eA[4], DB[4], mB[4], eB[4];
+        load(a.D[0], a.N[0], ax, ay, actA, 1.0, DA);
+        load(a.mu[0], a.N[0], ax, ay, actA, 1.0, mA);
+        load(a.q, a.N[0], ax, ay, actA, 0.0, A.q);
+        edges(a.D[0], a.N[0], ax, ay, actA, eA);
+        load(a.D[lB], a.N[lB], bx, by, actB, 1.0, DB);
+        load(a.mu[lB], a.N[lB], bx, by, actB, 1.0, mB);
+        edges(a.D[lB], a.N[lB], bx, by, actB, eB);
+        for (int i = tid; i < kS2Words; i += 1024) base[i] = 0.0;
+        if (tid < 16) sinv[tid] = a.cinv[tid];
+        __syncthreads();
+        auto put = [&](int id, int N, int x, int y, bool on, const double* D, const double* e) {
+            // the low y faces' D is only boundary vertices' neighbour
+#pragma unroll
+            for (int o = 0; o < 4; o++)
+                if (on && (y > 0 || (o & 1))) base[id + o * kS2S] = D[o];
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                if (on && x == N / 2 - 1) base[id + k * kS2S + kS2X] = e[k];
+                if (on && y == N / 2 - 1) base[id + 2 * k * kS2S + 1] = e[2 + k];
+            }
+        };
+        put(idA, a.N[0], ax, ay, actA, DA, eA);
+        put(idB, a.N[lB], bx, by, actB, DB, eB);
+        __syncthreads();
+        auto keep = [&](int x, int y, bool on, bool* k) {
+#pragma unroll
+            for (int o = 0; o < 4; o++) k[o] = on && (x > 0 || (o & 2)) && (y > 0 || (o & 1));
+        };
+        bool kA[4], kB[4];
+        keep(ax, ay, actA, kA);
+        keep(bx, by, actB, kB);
+        A.coefs<HARM, kS2S, kS2X>(base, idA, DA, mA, kA, a.st[0]);
+        if (hasB) B.coefs<HARM, kS2S, kS2X>(base, idB, DB, mB, kB, a.st[lB]);
+        __syncthreads();
+        // the vertices past the end are boundary: 0 from here on
+        const double zero[4] = {0.0, 0.0, 0.0, 0.0};
+        put(idA, a.N[0], ax, ay, actA, zero, zero);
+        put(idB, a.N[lB], bx, by, actB, zero, zero);
     }
-    __syncthreads();
-    auto half = [&](int i, int colour) {
-        const int N = a.N[i], n = N + 1, S = N / 2;
-        const Stencil<double> s = a.st[i];
-        double* u = U(i);
-        for (int t = tid; t < (N - 1) * S; t += nt) {
-            const int x = 1 + t / S;
-            const int y = (((colour - x) & 1) ? 1 : 2) + 2 * (t % S);
-            if (y >= N) continue;
-            const int v = x * n + y;
-            const double Di = DD(i)[v];
-            const double cxm = face<HARM>(Di, DD(i)[v - n], s), cxp = face<HARM>(Di, DD(i)[v + n], s);
-            const double cym = face<HARM>(Di, DD(i)[v - 1], s), cyp = face<HARM>(Di, DD(i)[v + 1], s);
-            u[v] = (Q(i)[v] + cxm * u[v - n] + cxp * u[v + n] + cym * u[v - 1] + cyp * u[v + 1]) /
-                   (cxm + cxp + cym + cyp + M(i)[v]);
+    // levels 0 and 1 are shared by several waves: their steps end with a
+    // workgroup barrier, which every wave joins
+    auto sync = [&](int l) {
+        if (l <= 1) {
+            __syncthreads();
+        } else if (lb == l) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+    };
+    auto sweeps = [&](int l, bool run, Block2& P, int id, int count, bool skip1) {
+        for (int c = 0; c < 2 * count; c++) {
+            if (skip1 && c == 0) continue;
+            if (run) {
+                if (((c & 1) ? 1 - first : first)) P.half<1, kS2S, kS2X, false>(base, id);
+                else P.half<0, kS2S, kS2X, false>(base, id);
+            }
+            sync(l);
+        }
+    };
+    auto down = [&](int l, bool run, Block2& P, int id, int x, int y) {
+        if (run) {
+            // from zero the first half-sweep is u = w q on the first colour
+#pragma unroll
+            for (int o = 0; o < 4; o++) {
+                if (l > 0) P.q[o] = base[id + o * kS2S];
+                P.u[o] = (a.nu_pre > 0 && (__builtin_popcount(o) & 1) == first) ? P.w[o] * P.q[o] : 0.0;
+            }
+#pragma unroll
+            for (int o = 0; o < 4; o++) base[id + o * kS2S] = P.u[o];
+        }
+        sync(l);
+        sweeps(l, run, P, id, a.nu_pre, true);
+        double r[4] = {};
+        if (run) {
+            if (a.nu_pre == 0) {
+#pragma unroll
+                for (int o = 0; o < 4; o++) r[o] = P.w[o] == 0.0 ? 0.0 : P.q[o];
+            } else if (first) {
+                P.residual<1, kS2S, kS2X>(base, id, r);
+            } else {
+                P.residual<0, kS2S, kS2X>(base, id, r);
+            }
+        }
+        sync(l);
+        if (run) {
+#pragma unroll
+            for (int o = 0; o < 4; o++) base[id + o * kS2S] = r[o];
+        }
+        sync(l);
+        if (run && x > 0 && y > 0)
+            base[small2_at(small2_off(l + 1), x, y)] = Block2::restricted<kS2S, kS2X>(base, id);
         __syncthreads();
     };
-    auto sweeps = [&](int i, int count) {
-        for (int c = 0; c < count; c++) {
-            half(i, a.first);
-            half(i, 1 - a.first);
+    auto up = [&](int l, bool run, Block2& P, int id, int x, int y) {
+        if (run) {
+            double E[4];
+#pragma unroll
+            for (int o = 0; o < 4; o++) E[o] = base[small2_at(small2_off(l + 1), x + (o >> 1), y + (o & 1))];
+            const double e[4] = {E[0], 0.5 * (E[0] + E[1]), 0.5 * (E[0] + E[2]), 0.25 * ((E[0] + E[2]) + (E[1] + E[3]))};
+#pragma unroll
+            for (int o = 0; o < 4; o++) {
+                if (P.w[o] != 0.0) P.u[o] += e[o];
+                base[id + o * kS2S] = P.u[o];
+            }
         }
+        sync(l);
+        sweeps(l, run, P, id, a.nu_post, false);
+        if (l > 1) __syncthreads();   // the finer level's waves read the result
     };
-    for (int i = 0; i + 1 < a.nl; i++) {
-        sweeps(i, a.nu_pre);
-        // qc = R (q - A u)
-        const int Nf = a.N[i], nf = Nf + 1, Nc = a.N[i + 1], nc = Nc + 1;
-        const Stencil<double> s = a.st[i];
-        for (int v = tid; v < (Nc - 1) * (Nc - 1); v += nt) {
-            const int X = 1 + v / (Nc - 1), Y = 1 + v % (Nc - 1);
+    down(0, actA, A, idA, ax, ay);
+    for (int l = 1; l < L - 1; l++) down(l, actB && lb == l, B, idB, bx, by);
+    {
+        const int N = a.N[L - 1], m1 = N - 1, m = m1 * m1, off = small2_off(L - 1);
+        if (tid < m) {
             double acc = 0.0;
-            for (int da = -1; da <= 1; da++) {
-                double row = 0.0;
-                for (int db = -1; db <= 1; db++) {
-                    const int f = (2 * X + da) * nf + 2 * Y + db;
-                    const double Di = DD(i)[f], ui = U(i)[f];
-                    const double r = Q(i)[f] - (M(i)[f] * ui + face<HARM>(Di, DD(i)[f - nf], s) * (ui - U(i)[f - nf]) +
-                                                face<HARM>(Di, DD(i)[f + nf], s) * (ui - U(i)[f + nf]) +
-                                                face<HARM>(Di, DD(i)[f - 1], s) * (ui - U(i)[f - 1]) +
-                                                face<HARM>(Di, DD(i)[f + 1], s) * (ui - U(i)[f + 1]));
-                    row += (db == 0 ? 2.0 : 1.0) * r;
-                }
-                acc += (double)(2 - abs(da)) * row;
-            }
-            Q(i + 1)[X * nc + Y] = acc * (1.0 / 16.0);
+            for (int c = 0; c < m; c++) acc += sinv[4 * tid + c] * base[small2_at(off, 1 + c / m1, 1 + c % m1)];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            base[small2_at(off, 1 + tid / m1, 1 + tid % m1)] = acc;
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        // exact solve on the coarsest level (N in {2, 3}), zero boundary
-        const int i = a.nl - 1, N = a.N[i], n = N + 1, m1 = N - 1, m = m1 * m1;
-        const Stencil<double> s = a.st[i];
-        double A[4][4], b[4];
-        for (int r = 0; r < m; r++)
-            for (int c = 0; c < m; c++) A[r][c] = 0.0;
-        for (int x = 1; x < N; x++)
-            for (int y = 1; y < N; y++) {
-                const int t = (x - 1) * m1 + (y - 1), v = x * n + y;
-                A[t][t] = M(i)[v];
-                b[t] = Q(i)[v];
-                const int nb[4][2] = {{x - 1, y}, {x + 1, y}, {x, y - 1}, {x, y + 1}};
-                for (int e = 0; e < 4; e++) {
-                    const int xa = nb[e][0], ya = nb[e][1];
-                    const double c = face<HARM>(DD(i)[v], DD(i)[xa * n + ya], s);
-                    A[t][t] += c;
-                    if (xa > 0 && xa < N && ya > 0 && ya < N) A[t][(xa - 1) * m1 + (ya - 1)] -= c;
-                }
-            }
-        for (int j = 0; j < m; j++) {
-            double d = A[j][j];
-            for (int p = 0; p < j; p++) d -= A[j][p] * A[j][p];
-            d = sqrt(d);
-            A[j][j] = d;
-            for (int r = j + 1; r < m; r++) {
-                double acc = A[r][j];
-                for (int p = 0; p < j; p++) acc -= A[r][p] * A[j][p];
-                A[r][j] = acc / d;
-            }
-        }
-        for (int r = 0; r < m; r++) {
-            double acc = b[r];
-            for (int p = 0; p < r; p++) acc -= A[r][p] * b[p];
-            b[r] = acc / A[r][r];
-        }
-        for (int r = m - 1; r >= 0; r--) {
-            double acc = b[r];
-            for (int p = r + 1; p < m; p++) acc -= A[p][r] * b[p];
-            b[r] = acc / A[r][r];
-        }
-        for (int x = 1; x < N; x++)
-            for (int y = 1; y < N; y++) U(i)[x * n + y] = b[(x - 1) * m1 + (y - 1)];
+    for (int l = L - 2; l >= 1; l--) up(l, actB && lb == l, B, idB, bx, by);
+    up(0, actA, A, idA, ax, ay);
+    if (actA) {
+#pragma unroll
+        for (int o = 0; o < 4; o++)
+            if (A.w[o] != 0.0) a.u[(2 * ax + (o >> 1)) * (a.N[0] + 1) + 2 * ay + (o & 1)] = A.u[o];
     }
-    __syncthreads();
-    for (int i = a.nl - 2; i >= 0; i--) {
-        // u += I uc on fine interior vertices
-        const int Nf = a.N[i], nf = Nf + 1, nc = a.N[i + 1] + 1;
-        const double* ec = U(i + 1);
-        for (int v = tid; v < nf * nf; v += nt) {
-            const int x = v / nf, y = v % nf;
-            if (x == 0 || x == Nf || y == 0 || y == Nf) continue;
-            const int X0 = x >> 1, X1 = (x + 1) >> 1, Y0 = y >> 1, Y1 = (y + 1) >> 1;
-            const double* r0 = ec + X0 * nc;
-            const double* r1 = ec + X1 * nc;
-            double e;
-            if (X0 == X1) e = (Y0 == Y1) ? r0[Y0] : 0.5 * (r0[Y0] + r0[Y1]);
-            else if (Y0 == Y1) e = 0.5 * (r0[Y0] + r1[Y0]);
-            else e = 0.25 * (r0[Y0] + r1[Y0] + r0[Y1] + r1[Y1]);
-            U(i)[v] += e;
-        }
-        __syncthreads();
-        sweeps(i, a.nu_post);
-    }
-    const int nv0 = (a.N[0] + 1) * (a.N[0] + 1);
-    for (int v = tid; v < nv0; v += nt) a.u[v] = U(0)[v];
-#undef U
-#undef Q
-#undef DD
-#undef M
 }
-
-}  // namespace dmgs
-
-namespace dmgs {
 
 // ---------------------------------------------------------------------------
 // A whole smoothing phase of a mid-size level in one launch: one workgroup
-// per 32 x 32 tile, the tile and a ring of kH2 = 6 vertices staged in LDS
-// (u, q, D, mua), two red-black sweeps (four half-sweeps) with a barrier
-// after each, half-sweep j updating the tile plus a shrinking ring.
-//   MODE 0 / 1 (pre-smoothing from u_in / from zero): the sweeps leave u
-//     final on the tile plus a ring of 2; the pass writes u on the tile and
-//     the restricted defect qc = R (q - A u) of the tile's 16 x 16 coarse
-//     vertices (each forms its nine fine defects from LDS).
-//   MODE 2 (post-smoothing): u_in + I ec (bilinear, the bilinear weights of
-//     k2_prolong_add) is staged, then the sweeps; the pass writes u on the
-//     tile.
-// Only interior grid vertices are updated or written; staged vertices
-// outside the grid hold u = q = mua = 0, D = 1 and are never updated.
-constexpr int kB2 = 32, kH2 = 6, kW2 = kB2 + 2 * kH2;
+// per tile, the tile and a ring around it as NB x NB register blocks.
+//   MODE 0 / 1 (pre-smoothing from u_in / from zero): two red-black sweeps
+//     from a ring of 6 leave u final on the tile plus a ring of 2; the pass
+//     writes u on the tile and the restricted defect qc = R (q - A u) of its
+//     coarse vertices.
+//   MODE 2 (post-smoothing): u_in + I ec (bilinear, the weights of
+//     k2_prolong_add), two sweeps from a ring of 4, u on the tile.
+// Every block of the box is updated in all four half-sweeps.  A vertex j
+// rings inside the box has the sequential sweeps' value after half-sweep j;
+// what is formed nearer to the edge, from neighbours the box does not hold,
+// is finite and read by nothing that is kept.  Only interior grid vertices
+// are updated or written.
+//
+// Bound by latency up to 512^2 (one round of workgroups: load, four
+// half-sweeps, store) and above by the loads of the box.  Measured
+// (pre- / post-smoothing): 128^2 .. 512^2 5 us each, 1024^2 13 / 13 us, 4096^2
+// 172 / 151 us (5.1 TB/s of one read of u, q, D, mua and one write of u).
+// Holding u, q, D and mua in LDS and dividing by the diagonal in every update
+// took 14 / 17 us at 128^2 .. 512^2 and 35 / 40 us at 1024^2; the row-marching
+// passes 84 / 62 us at 2048^2 and 242 / 192 us at 4096^2 (with the separate
+// restriction).
+//
+// 22 x 22 blocks: with 32 x 32 (1.5 instead of 1.9 times the tile loaded, 1024
+// threads) too few workgroups share a CU to overlap one's loads with
+// another's half-sweeps, 14 -> 17 us at 1024^2 and 172 -> 233 us at 4096^2.
+constexpr int kNb2 = 22;
+constexpr int kB2X = kNb2 + 2, kB2S = kB2X * (kNb2 + 2);        // LDS strides: one unused block on every side
+constexpr int kB2Threads = (kNb2 * kNb2 + 63) / 64 * 64;
+__host__ __device__ constexpr int block2_ring(int mode) { return mode == 2 ? 4 : 6; }
+__host__ __device__ constexpr int block2_tile(int mode) { return 2 * kNb2 - 2 * block2_ring(mode); }
 
 template <bool HARM, int MODE>
-__global__ __launch_bounds__(256) void k2_block_pass(const double* __restrict__ uin, double* __restrict__ uout,
-                                                     const double* __restrict__ q, const double* __restrict__ D,
-                                                     const double* __restrict__ mu, const double* __restrict__ ec,
-                                                     double* __restrict__ qc, int N, Stencil<double> st, int first,
-                                                     int ntx) {
-    __shared__ double su[kW2 * kW2], sq[kW2 * kW2], sd[kW2 * kW2], sm[kW2 * kW2];
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int tx = blockIdx.x % ntx, ty = blockIdx.x / ntx;
-    const int x0 = tx * kB2 - kH2, y0 = ty * kB2 - kH2;   // grid coordinates of LDS entry (0, 0)
+__global__ __launch_bounds__(kB2Threads) void k2_block_pass(
+    const double* __restrict__ uin, double* __restrict__ uout, const double* __restrict__ q, const double* __restrict__ D,
+    const double* __restrict__ mu, const double* __restrict__ ec, double* __restrict__ qc, int N, Stencil<double> st,
+    int first, int ntx) {
+    constexpr int kB2 = block2_tile(MODE), kH2 = block2_ring(MODE);
+    __shared__ double base[4 * kB2S];
+    const int tid = threadIdx.x;
+    const bool act = tid < kNb2 * kNb2;
+    const int lx = act ? tid / kNb2 : 0, ly = act ? tid % kNb2 : 0;
+    const int tile_id = xcd_remap(blockIdx.x, gridDim.x), tx = tile_id / ntx, ty = tile_id % ntx;
+    const int gx = tx * kB2 - kH2 + 2 * lx, gy = ty * kB2 - kH2 + 2 * ly;   // the corner (even)
     const int n = N + 1, Nc = N / 2, nc = Nc + 1;
-    for (int i = tid; i < kW2 * kW2; i += nt) {
-        const int gx = x0 + i / kW2, gy = y0 + i % kW2;
-        const bool in = gx >= 0 && gx <= N && gy >= 0 && gy <= N;
-        const int64_t g = (int64_t)gx * n + gy;
-        sd[i] = in ? D[g] : 1.0;
-        sm[i] = in ? mu[g] : 0.0;
-        sq[i] = in ? q[g] : 0.0;
-        double u = 0.0;
-        if (MODE == 0 || MODE == 2) u = in ? uin[g] : 0.0;
-        if (MODE == 2 && in && gx > 0 && gx < N && gy > 0 && gy < N) {
-            const int X0 = gx >> 1, X1 = (gx + 1) >> 1, Y0 = gy >> 1, Y1 = (gy + 1) >> 1;
-            const double* r0 = ec + (int64_t)X0 * nc;
-            const double* r1 = ec + (int64_t)X1 * nc;
-            double e;
-            if (X0 == X1) e = (Y0 == Y1) ? r0[Y0] : 0.5 * (r0[Y0] + r0[Y1]);
-            else if (Y0 == Y1) e = 0.5 * (r0[Y0] + r1[Y0]);
-            else e = 0.25 * (r0[Y0] + r1[Y0] + r0[Y1] + r1[Y1]);
-            u += e;
+    const int id = (lx + 1) * kB2X + ly + 1;
+    Block2 P;
+    bool in[4], keep[4];
+#pragma unroll
+    for (int o = 0; o < 4; o++) {
+        const int x = gx + (o >> 1), y = gy + (o & 1);
+        in[o] = act && x >= 0 && x <= N && y >= 0 && y <= N;
+        keep[o] = act && interior2(N, x, y);
+    }
+    {
+        // rows of the block as 16-byte loads (8-byte aligned); vertices outside
+        // the grid: a clamped read, replaced.  At y = N the pair read is
+        // (N - 1, N).
+        const int yc = min(max(gy, 0), N - 1);
+        const int g0 = min(max(gx, 0), N) * n + yc, g1 = min(max(gx + 1, 0), N) * n + yc;
+        auto load = [&](const double* p, double* v) {
+            const Pair2 r0 = *reinterpret_cast<const Pair2*>(p + g0), r1 = *reinterpret_cast<const Pair2*>(p + g1);
+            v[0] = gy == N ? r0.b : r0.a;
+            v[1] = r0.b;
+            v[2] = gy == N ? r1.b : r1.a;
+            v[3] = r1.b;
+        };
+        double Dv[4], mv[4];
+        load(D, Dv);
+        load(mu, mv);
+        load(q, P.q);
+        if (MODE == 1) {
+#pragma unroll
+            for (int o = 0; o < 4; o++) P.u[o] = 0.0;
+        } else {
+            load(uin, P.u);
         }
-        su[i] = u;
+        if (MODE == 2) {
+            // the block's four coarse neighbours, from the corner's
+            const int X0 = min(max(gx >> 1, 0), Nc), X1 = min(X0 + 1, Nc), Y0 = min(max(gy >> 1, 0), Nc), Y1 = min(Y0 + 1, Nc);
+            const double e00 = ec[X0 * nc + Y0], e01 = ec[X0 * nc + Y1], e10 = ec[X1 * nc + Y0], e11 = ec[X1 * nc + Y1];
+            const double e[4] = {e00, 0.5 * (e00 + e01), 0.5 * (e00 + e10), 0.25 * ((e00 + e10) + (e01 + e11))};
+#pragma unroll
+            for (int o = 0; o < 4; o++) P.u[o] += keep[o] ? e[o] : 0.0;
+        }
+        for (int i = tid; i < 4 * kB2S; i += kB2Threads) base[i] = 1.0;   // any finite D > 0 beyond the box
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < 4; o++) {
+            if (!in[o]) P.u[o] = P.q[o] = 0.0;
+            if (act) base[id + o * kB2S] = Dv[o];
+        }
+        __syncthreads();
+        P.coefs<HARM, kB2S, kB2X>(base, id, Dv, mv, keep, st);
+        __syncthreads();
+    }
+    if (act) {
+#pragma unroll
+        for (int o = 0; o < 4; o++) base[id + o * kB2S] = P.u[o];
     }
     __syncthreads();
-    const int ring0 = MODE == 2 ? 3 : 5;   // ring of the first half-sweep
     for (int j = 0; j < 4; j++) {
-        const int colour = (j & 1) ? 1 - first : first, ring = ring0 - j;
-        const int lo = kH2 - ring, hi = kH2 + kB2 + ring;   // local range [lo, hi)
-        for (int i = tid; i < kW2 * kW2; i += nt) {
-            const int lx = i / kW2, ly = i % kW2, gx = x0 + lx, gy = y0 + ly;
-            if (lx < lo || lx >= hi || ly < lo || ly >= hi || ((gx + gy) & 1) != colour) continue;
-            if (gx < 1 || gx > N - 1 || gy < 1 || gy > N - 1) continue;
-            const double Di = sd[i];
-            const double cxm = face<HARM>(Di, sd[i - kW2], st), cxp = face<HARM>(Di, sd[i + kW2], st);
-            const double cym = face<HARM>(Di, sd[i - 1], st), cyp = face<HARM>(Di, sd[i + 1], st);
-            su[i] = (sq[i] + cxm * su[i - kW2] + cxp * su[i + kW2] + cym * su[i - 1] + cyp * su[i + 1]) /
-                    (cxm + cxp + cym + cyp + sm[i]);
+        if (act) {
+            if ((j & 1) ? !first : first) P.half<1, kB2S, kB2X, true>(base, id);
+            else P.half<0, kB2S, kB2X, true>(base, id);
         }
         __syncthreads();
     }
-    for (int i = tid; i < kB2 * kB2; i += nt) {
-        const int lx = kH2 + i / kB2, ly = kH2 + i % kB2, gx = x0 + lx, gy = y0 + ly;
-        if (gx < 1 || gx > N - 1 || gy < 1 || gy > N - 1) continue;
-        uout[(int64_t)gx * n + gy] = su[lx * kW2 + ly];
-    }
+    constexpr int H = kH2 / 2, T = kB2 / 2;   // ring and tile in blocks
+    const bool tile = lx >= H && lx < H + T && ly >= H && ly < H + T;
+#pragma unroll
+    for (int o = 0; o < 4; o++)
+        if (tile && keep[o]) uout[(gx + (o >> 1)) * n + gy + (o & 1)] = P.u[o];
     if (MODE == 2) return;
-    // restriction of the defect to the tile's coarse vertices (one per thread)
-    for (int c = tid; c < (kB2 / 2) * (kB2 / 2); c += nt) {
-        const int X = tx * (kB2 / 2) + c / (kB2 / 2), Y = ty * (kB2 / 2) + c % (kB2 / 2);
-        if (X < 1 || X > Nc - 1 || Y < 1 || Y > Nc - 1) continue;
-        double acc = 0.0;
-        for (int a = -1; a <= 1; a++) {
-            double row = 0.0;
-            for (int b = -1; b <= 1; b++) {
-                const int i = (2 * X + a - x0) * kW2 + (2 * Y + b - y0);
-                const double Di = sd[i], ui = su[i];
-                const double r = sq[i] - (sm[i] * ui + face<HARM>(Di, sd[i - kW2], st) * (ui - su[i - kW2]) +
-                                          face<HARM>(Di, sd[i + kW2], st) * (ui - su[i + kW2]) +
-                                          face<HARM>(Di, sd[i - 1], st) * (ui - su[i - 1]) +
-                                          face<HARM>(Di, sd[i + 1], st) * (ui - su[i + 1]));
-                row += (b == 0 ? 2.0 : 1.0) * r;
-            }
-            acc += (double)(2 - abs(a)) * row;
-        }
-        qc[(int64_t)X * nc + Y] = acc * (1.0 / 16.0);
+    // restriction of the defect: a coarse vertex is the corner of its block
+    double r[4] = {};
+    if (act) {
+        if (first) P.residual<1, kB2S, kB2X>(base, id, r);
+        else P.residual<0, kB2S, kB2X>(base, id, r);
     }
+    __syncthreads();
+    if (act) {
+#pragma unroll
+        for (int o = 0; o < 4; o++) base[id + o * kB2S] = r[o];
+    }
+    __syncthreads();
+    if (tile && keep[0]) qc[(gx >> 1) * nc + (gy >> 1)] = Block2::restricted<kB2S, kB2X>(base, id);
 }
 
 }  // namespace dmgs

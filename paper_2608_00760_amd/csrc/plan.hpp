@@ -106,9 +106,9 @@ struct dmgs_plan_s {
     int cfg_block_max = 64;                         // block passes: largest N
     int cfg_dr_wgs = 512;                           // defect-restriction passes: target workgroups
     int cfg_defect = 2;   // two-sweep pre-smoothing writes the defect: 0 never, 1 from a zero iterate, 2 always
-    int cfg_2d_sweep2_min = 1536;  // two-dimensional plans: smallest N of the two-sweep passes
+    int cfg_2d_sweep2_min = 1536;  // two-dimensional plans: smallest N of the row-marching two-sweep passes
     bool cfg_sweep2_fp64 = true;   // float64 levels use the two-sweep passes (zero boundaries only)
-    int cfg_2d_block_min = 64;     // two-dimensional plans: smallest N of the LDS block passes
+    int cfg_2d_block_min = 4;      // two-dimensional plans: smallest N of the block passes
     bool cfg_2d_defect = true;     // ... the last pre-smoothing pass writes the defect
     bool cfg_epi_fuse = true;      // the likelihood epilogue rides on the last refinement step
     bool cfg_trace = false;        // DMGS_TRACE: record each solve's residual history
