@@ -124,8 +124,7 @@ typedef struct dmgs_options {
     double h_axis[3];      /* three-dimensional plans: spacing per axis (x, y, z); 0 (default) = h.  Unequal
                               counts in n or unequal spacings make a general-grid plan: the face
                               coefficient of each axis is D_f / h_a^2, on level k with 2^k h_a (Sec. 2.2
-                              rediscretised per axis); DMGS_FP64 and DMGS_RBGS only, one operation per
-                              launch; every solve, push-forward, pull-back and likelihood entry point
+                              rediscretised per axis); DMGS_FP64 and DMGS_RBGS only; every solve, push-forward, pull-back and likelihood entry point
                               takes them (dmgs_forward_vjp runs its two solves one after the other);
                               the diagnostic entry points and dmgs_vjp_unrolled do not. */
 } dmgs_options;
@@ -173,7 +172,7 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options *opt);
  *   DMGS_SWEEP2_FP64 (1)        float64 levels with a zero boundary use the two-sweep pass
  *   DMGS_SWEEP_CFG (0)          float32 one-sweep pass tiles: 0 16x64, 1 8x64, 2 16x32
  *   DMGS_FUSE_MIN (32 / 16)     smallest N of the fused passes (float32 / float64 plans)
- *   DMGS_BLOCK_MAX (64)         largest N of the LDS block passes
+ *   DMGS_BLOCK_MAX (64)         largest N of the register-block passes
  *   DMGS_DR_WGS (512 / 1024)    target workgroups of the defect-restriction pass (float32 / float64 plans)
  *   DMGS_2D_SWEEP2_MIN          two-dimensional plans: smallest N of the row-marching two-sweep
  *                               passes (unset: none in V(2,2) plans, whose levels run the block

@@ -847,76 +847,144 @@ int coarsest(dmgs_plan P, const T* q, T* u, hipStream_t st) {
 
 bool fused_level(dmgs_plan P, int k) { return P->lev[k].N >= P->cfg_fuse_min && k < P->L - 1; }
 
-// Mid-size float32 levels run each smoothing phase as one block launch
-// (zero boundary: the refinement corrections; two sweeps each way).
+// Mid-size levels run each smoothing phase as one launch of register blocks
+// (two sweeps each way).  Float32: the refinement corrections above the
+// coarse kernel's levels.  Float64: every cubic level up to the same size,
+// the finest included, and every level of a general grid.
 template <class T>
 bool block_level(dmgs_plan P, int k) {
+    if (P->opt.nu_pre != 2 || P->opt.nu_post != 2 || k >= P->L - 1 || P->opt.smoother != DMGS_RBGS) return false;
+    if (P->grid) return sizeof(T) == 8;
     const int N = P->lev[k].N;
-    return sizeof(T) == 4 && is_ir(P) && k < P->L - 1 && N > 16 && N <= P->cfg_block_max && P->opt.nu_pre == 2 &&
-           P->opt.nu_post == 2;
+    return (sizeof(T) == 4) == is_ir(P) && N <= P->cfg_block_max && (N > 16 || (sizeof(T) == 8 && k == 0 && N >= 4));
 }
-
-constexpr int kBlockB = 8;
 
 template <class T, int MODE, bool HARM>
-int launch_block_t(dmgs_plan P, const BlockArgs<T>& a, hipStream_t st) {
-    const int nb3 = a.nb * a.nb * a.nb;
-    const size_t lds = BlockShape<kBlockB, MODE>::lds_bytes(sizeof(T));
-    return launch_rec(P, (const void*)k_block_pass<T, kBlockB, MODE, HARM>, (const void*)k_block_grp<T, kBlockB, MODE, HARM>,
-                      (unsigned)nb3, kBlockThreads, lds, a, st);
+int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st, unsigned* nb_out) {
+    const Level& l = P->lev[k];
+    unsigned nb = 1;
+    for (int x = 0; x < 3; x++) {
+        a.n[x] = l.nc[x];
+        a.s[x] = (T)((HARM ? 2.0 : 0.5) / (l.h3[x] * l.h3[x]));
+        a.nt[x] = Block3Shape<MODE, false>::tiles(l.nc[x]);
+        nb *= (unsigned)a.nt[x];
+    }
+    if (nb_out) *nb_out = nb;
+    if constexpr (MODE == kB3PostEpi) {
+        a.w = l.mu64;
+        hipLaunchKernelGGL((k_block3<T, MODE, HARM, true>), dim3(nb), dim3(Block3Shape<MODE, true>::NT),
+                           (block3_lds<T, MODE, true>()), st, a);
+        LAUNCHCHK();
+        return DMGS_OK;
+    } else if constexpr (sizeof(T) == 8) {
+        if (P->grid) {
+            a.w = Typed<T>::mu(l);
+            hipLaunchKernelGGL((k_block3<T, MODE, HARM, true>), dim3(nb), dim3(Block3Shape<MODE, true>::NT),
+                               (block3_lds<T, MODE, true>()), st, a);
+        } else {
+            hipLaunchKernelGGL((k_block3<T, MODE, HARM, false>), dim3(nb), dim3(Block3Shape<MODE, false>::NT),
+                               (block3_lds<T, MODE, false>()), st, a);
+        }
+        LAUNCHCHK();
+        return DMGS_OK;
+    } else {
+        return launch_rec(P, (const void*)k_block3<T, MODE, HARM, false>, (const void*)k_block3_grp<T, MODE, HARM>, nb,
+                          Block3Shape<MODE, false>::NT, block3_lds<T, MODE, false>(), a, st);
+    }
 }
 
-// One block phase on level k: pre (from *cur or from zero; qc written) or
-// post (*cur + I ec); the result goes to *other and the buffers swap.
+// One block launch on level k (Block3Mode): u_in, u_out, the correction ec
+// and the restricted defect qc as the mode takes them; kB3Sweep with partial
+// also sums the squares of u_in's residual per workgroup (*nb_out of them).
 template <class T>
-int block_phase(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, const T* ec, int order, bool zero,
-                bool post, hipStream_t st) {
+int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T* q, const T* ec, T* qc, int order,
+                 hipStream_t st, double* partial = nullptr, unsigned* nb_out = nullptr) {
     const Level& l = P->lev[k];
-    TRY(need_dense<T>(P, k, "block pass"));
-    BlockArgs<T> a;
-    a.u_in = *cur;
-    a.u_out = *other;
+    if (!P->grid) TRY(need_dense<T>(P, k, "block pass"));
+    Block3Args<T> a{};
+    a.u_in = u_in;
+    a.u_out = u_out;
     a.q = q;
     a.D = Typed<T>::D(l);
     a.w = Typed<T>::w(l);
     a.ec = ec;
     a.qc = qc;
-    a.N = l.N;
-    a.nb = (l.N - 1 + kBlockB - 1) / kBlockB;
+    a.partial = partial;
     a.order = order;
-    a.st = l.stencil<T>(harmonic(P));
-    const int mode = post ? kBlockPost : (zero ? kBlockPreZero : kBlockPre);
-    const double words = (zero ? 4.0 : 5.0) + 0.125;
+    const bool h = harmonic(P);
+    // algorithmic bytes: q, D, w, and u read unless zero, u written, plus the
+    // coarse level's share
+    const double words = (mode == kB3PreZero ? 4.0 : mode == kB3Defect ? 4.0 : 5.0) + (mode == kB3Sweep ? 0.0 : 0.125);
+    const int cls = mode == kB3Defect ? DMGS_K_DEFECT_RESTRICT : DMGS_K_SMOOTH;
     int slot;
-    TRY(tbeg(P, k, st, &slot, DMGS_K_SMOOTH));
-    if constexpr (sizeof(T) == 4) {
-        const bool h = harmonic(P);
-        if (mode == kBlockPost) TRY(h ? (launch_block_t<T, kBlockPost, true>(P, a, st)) : (launch_block_t<T, kBlockPost, false>(P, a, st)));
-        else if (mode == kBlockPre) TRY(h ? (launch_block_t<T, kBlockPre, true>(P, a, st)) : (launch_block_t<T, kBlockPre, false>(P, a, st)));
-        else TRY(h ? (launch_block_t<T, kBlockPreZero, true>(P, a, st)) : (launch_block_t<T, kBlockPreZero, false>(P, a, st)));
-    } else {
-        set_error("block passes are float32 only");
-        return DMGS_ERR_INVALID;
+    TRY(tbeg(P, k, st, &slot, cls));
+    auto go = [&](auto Mc) -> int {
+        constexpr int M = decltype(Mc)::value;
+        return h ? launch_block3<T, M, true>(P, k, a, st, nb_out) : launch_block3<T, M, false>(P, k, a, st, nb_out);
+    };
+    switch (mode) {
+        case kB3PreZero: TRY(go(std::integral_constant<int, kB3PreZero>())); break;
+        case kB3Post: TRY(go(std::integral_constant<int, kB3Post>())); break;
+        default:
+            if constexpr (sizeof(T) == 4) {
+                if (mode != kB3Pre) { set_error("internal: float32 block pass of mode %d", mode); return DMGS_ERR_INVALID; }
+                TRY(go(std::integral_constant<int, kB3Pre>()));
+            } else if (mode == kB3Sweep) {
+                TRY(go(std::integral_constant<int, kB3Sweep>()));
+            } else if (mode == kB3Defect) {
+                TRY(go(std::integral_constant<int, kB3Defect>()));
+            } else if (mode == kB3PostEpi && P->grid) {
+                a.ed = P->epi_d;
+                a.ew = P->epi_w;
+                a.rhobar = P->epi_rhobar;
+                TRY(go(std::integral_constant<int, kB3PostEpi>()));
+            } else {
+                set_error("internal: float64 block pass of mode %d", mode);
+                return DMGS_ERR_INVALID;
+            }
     }
-    TRY(tend(P, slot, DMGS_K_SMOOTH, words * l.nv * sizeof(T), st));
+    return tend(P, slot, cls, words * l.nv * sizeof(T), st);
+}
+
+// Pre-smoothing phase of a block level from *cur (or from zero), qc = R (q -
+// A u); the result goes to *other and the buffers swap.
+template <class T>
+int block_pre(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int order, bool zero, hipStream_t st) {
+    const T* none = nullptr;
+    if (zero || sizeof(T) == 4) {
+        TRY(block_launch<T>(P, k, zero ? kB3PreZero : kB3Pre, *cur, *other, q, none, qc, order, st));
+        std::swap(*cur, *other);
+        return DMGS_OK;
+    }
+    TRY(block_launch<T>(P, k, kB3Sweep, *cur, *other, q, none, (T*)nullptr, order, st));
+    std::swap(*cur, *other);
+    return block_launch<T>(P, k, kB3Defect, *cur, (T*)nullptr, q, none, qc, order, st);
+}
+
+// Workgroups (and norm partials) of a kB3Sweep launch on level k.
+int64_t block_sweep_blocks(dmgs_plan P, int k) {
+    int64_t nb = 1;
+    for (int x = 0; x < 3; x++) nb *= Block3Shape<kB3Sweep, false>::tiles(P->lev[k].nc[x]);
+    return nb;
+}
+
+// Post-smoothing phase: u = *cur + I ec, two sweeps.
+template <class T>
+int block_post(dmgs_plan P, int k, T** cur, T** other, const T* q, const T* ec, int order, hipStream_t st) {
+    TRY(block_launch<T>(P, k, kB3Post, *cur, *other, q, ec, (T*)nullptr, order, st));
     std::swap(*cur, *other);
     return DMGS_OK;
 }
 
-// Dynamic-LDS limits of the block kernels (set once per plan).
+// Dynamic-LDS limits of the block kernels whose box exceeds the default.
 int block_attributes() {
-    const void* fns[] = {
-        (const void*)k_block_pass<float, kBlockB, kBlockPreZero, false>, (const void*)k_block_pass<float, kBlockB, kBlockPreZero, true>,
-        (const void*)k_block_pass<float, kBlockB, kBlockPre, false>, (const void*)k_block_pass<float, kBlockB, kBlockPre, true>,
-        (const void*)k_block_pass<float, kBlockB, kBlockPost, false>, (const void*)k_block_pass<float, kBlockB, kBlockPost, true>,
-        (const void*)k_block_grp<float, kBlockB, kBlockPreZero, false>, (const void*)k_block_grp<float, kBlockB, kBlockPreZero, true>,
-        (const void*)k_block_grp<float, kBlockB, kBlockPre, false>, (const void*)k_block_grp<float, kBlockB, kBlockPre, true>,
-        (const void*)k_block_grp<float, kBlockB, kBlockPost, false>, (const void*)k_block_grp<float, kBlockB, kBlockPost, true>};
-    const int lims[] = {(int)BlockShape<kBlockB, kBlockPreZero>::lds_bytes(4), (int)BlockShape<kBlockB, kBlockPreZero>::lds_bytes(4),
-                        (int)BlockShape<kBlockB, kBlockPre>::lds_bytes(4), (int)BlockShape<kBlockB, kBlockPre>::lds_bytes(4),
-                        (int)BlockShape<kBlockB, kBlockPost>::lds_bytes(4), (int)BlockShape<kBlockB, kBlockPost>::lds_bytes(4)};
-    for (int i = 0; i < 12; i++)
-        if (hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, lims[i % 6]) != hipSuccess) {
+    const std::pair<const void*, size_t> fns[] = {
+        {(const void*)k_block3<double, kB3PreZero, false, false>, block3_lds<double, kB3PreZero, false>()},
+        {(const void*)k_block3<double, kB3PreZero, true, false>, block3_lds<double, kB3PreZero, false>()},
+        {(const void*)k_block3<double, kB3PreZero, false, true>, block3_lds<double, kB3PreZero, true>()},
+        {(const void*)k_block3<double, kB3PreZero, true, true>, block3_lds<double, kB3PreZero, true>()}};
+    for (const auto& f : fns)
+        if (hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.second) != hipSuccess) {
             (void)hipGetLastError(); set_error("hipFuncSetAttribute failed");
             return DMGS_ERR_HIP;
         }
@@ -934,7 +1002,7 @@ int nu_post_of(dmgs_plan P, int order) { return order ? P->opt.nu_pre : P->opt.n
 template <class T>
 int pre_pass(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int order, bool zero, hipStream_t st) {
     const Level& l = P->lev[k];
-    if (block_level<T>(P, k)) return block_phase<T>(P, k, cur, other, q, qc, (const T*)nullptr, order, zero, false, st);
+    if (block_level<T>(P, k)) return block_pre<T>(P, k, cur, other, q, qc, order, zero, st);
     if (fused_level(P, k)) {
         bool rdone;
         T* r = Typed<T>::r(l);
@@ -956,7 +1024,7 @@ int pre_pass(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int orde
 template <class T>
 int post_pass(dmgs_plan P, int k, T** cur, T** other, const T* ec, const T* q, int order, hipStream_t st) {
     const Level& l = P->lev[k];
-    if (block_level<T>(P, k)) return block_phase<T>(P, k, cur, other, q, (T*)nullptr, ec, order, false, true, st);
+    if (block_level<T>(P, k)) return block_post<T>(P, k, cur, other, q, ec, order, st);
     if (fused_level(P, k)) return smooth_phase<T>(P, k, cur, other, q, nu_post_of(P, order), order, false, ec, st);
     TRY(need_dense<T>(P, k, "simple post-smoothing"));
     TIMED(P, k, DMGS_K_PROLONG, (double)(2 * l.nv + P->lev[k + 1].nv) * sizeof(T), st,
@@ -1071,7 +1139,9 @@ int vcycle(dmgs_plan P, int k, T** cur, T** other, const T* q, int order, bool z
     }
     const Level& c = P->lev[k + 1];
     T* qc = Typed<T>::q(c);
-    if (smoothed) TRY(rdone ? defect_restrict<T>(P, k, Typed<T>::r(P->lev[k]), q, qc, st, true, order)
+    if (smoothed && block_level<T>(P, k)) {
+        // the block pass has restricted the defect too
+    } else if (smoothed) TRY(rdone ? defect_restrict<T>(P, k, Typed<T>::r(P->lev[k]), q, qc, st, true, order)
                             : defect_restrict<T>(P, k, *cur, q, qc, st));
     else TRY(pre_pass<T>(P, k, cur, other, q, qc, order, zero, st));
     T* ccur = Typed<T>::u(c);
@@ -1540,6 +1610,46 @@ int vcycle_grid(dmgs_plan P, int k, double* u, const double* q, int order, hipSt
     return mark_norms(P, st);
 }
 
+// Post-smoothing of the finest level in register blocks; epi: with the
+// likelihood epilogue of the result, as in vcycle_grid.
+int post_grid_blocks(dmgs_plan P, double** cur, double** other, const double* q, const double* ec, int order,
+                     hipStream_t st, bool epi) {
+    if (!epi) return block_post<double>(P, 0, cur, other, q, ec, order, st);
+    unsigned nb = 0;
+    TRY(block_launch<double>(P, 0, kB3PostEpi, *cur, *other, q, ec, nullptr, order, st, P->partial, &nb));
+    std::swap(*cur, *other);
+    for (int i = 0; i < 2; i++) {
+        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial + i * nb, (int)nb,
+                           norm_dst(P), 2 + i);
+        LAUNCHCHK();
+    }
+    return mark_norms(P, st);
+}
+
+// The same cycle in register blocks (V(2,2)): *cur and *other are the
+// level's two buffers with the same boundary; zero: the iterate starts at 0.
+int vcycle_grid_blocks(dmgs_plan P, int k, double** cur, double** other, const double* q, int order, bool zero,
+                       hipStream_t st, bool epi = false) {
+    if (zero && k == P->small64) {
+        if (harmonic(P)) return launch_small_t<double, true>(P, k, q, *cur, order, st);
+        return launch_small_t<double, false>(P, k, q, *cur, order, st);
+    }
+    if (k == P->L - 1) {
+        const Level& l = P->lev[k];
+        hipLaunchKernelGGL(k_g_exact, dim3(1), dim3(kGridCoarseMax), 0, st, q, *cur, (const double*)l.D64,
+                           (const double*)P->cinv, gdims(P, k));
+        LAUNCHCHK();
+        return DMGS_OK;
+    }
+    const Level& c = P->lev[k + 1];
+    TRY(block_pre<double>(P, k, cur, other, q, c.q64, order, zero, st));
+    double* ccur = c.u64;
+    double* coth = c.t64;
+    TRY(vcycle_grid_blocks(P, k + 1, &ccur, &coth, c.q64, order, true, st));
+    if (k == 0) return post_grid_blocks(P, cur, other, q, ccur, order, st, epi);
+    return block_post<double>(P, k, cur, other, q, ccur, order, st);
+}
+
 // ||b - A x||^2 of the finest level into the norm slot `slot`.
 int resid_grid(dmgs_plan P, const double* x, const double* b, int slot, hipStream_t st) {
     const Level& l = P->lev[0];
@@ -1561,6 +1671,15 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
     const int nfix = replay ? (int)replay->size() : o.fixed_cycles;
     hipLaunchKernelGGL(k_g_init, dim3(grid_for(l0.nv)), dim3(kBlock), 0, st, x, gdims(P, 0), bc);
     LAUNCHCHK();
+    // V(2,2) cycles run in register blocks, out of place (the two buffers hold
+    // the same boundary); after a cycle the iterate is in x again
+    const bool blocks = block_level<double>(P, 0);
+    double* cur = x;
+    double* oth = l0.t64;
+    if (blocks) {
+        hipLaunchKernelGGL(k_g_init, dim3(grid_for(l0.nv)), dim3(kBlock), 0, st, oth, gdims(P, 0), bc);
+        LAUNCHCHK();
+    }
     int cycles = 0, status = DMGS_OK;
     double r0 = 0.0, rel = 0.0;
     // the initial residual into slot 0 (read in fixed mode only with info)
@@ -1580,15 +1699,56 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
     // cycle expected to be the last (in tolerance mode: the one the
     // contraction of the last cycle predicts to come within 4 rtol; a cycle
     // that takes it and is not the last costs one more read of d and w).
-    const bool want_epi = P->epi_d && order == 0;
+    const bool want_epi = P->epi_d && order == 0 && (!blocks || 2 * block_sweep_blocks(P, 0) <= kMaxPartials);
     P->epi_fused = false;
     double rel_prev = 1.0;
     bool epi_next = false;
+    // In register blocks the residual norm of an iterate comes with the next
+    // cycle's first sweeps, as on cubic float64 plans (see solve()).
+    const bool free_norm = blocks && !fixed && block_sweep_blocks(P, 0) <= kMaxPartials;
     if (status == DMGS_OK && (fixed || r0 > 0.0)) {
         for (cycles = 1; !(fixed && nfix == 0); cycles++) {
             bool done = false;
-            TRY(vcycle_grid(P, 0, x, b, order, st, want_epi && (fixed ? cycles == nfix : epi_next), &done));
+            if (free_norm && cycles >= 2) {
+                double* prev = cur;
+                unsigned nb = 0;
+                TRY(block_launch<double>(P, 0, kB3Sweep, cur, oth, b, nullptr, nullptr, order, st, P->partial, &nb));
+                std::swap(cur, oth);
+                hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial, (int)nb,
+                                   norm_dst(P), 1);
+                LAUNCHCHK();
+                TRY(mark_norms(P, st));
+                const Level& c1 = P->lev[1];
+                TRY(block_launch<double>(P, 0, kB3Defect, cur, nullptr, b, nullptr, c1.q64, order, st));
+                double* ccur = c1.u64;
+                double* coth = c1.t64;
+                TRY(vcycle_grid_blocks(P, 1, &ccur, &coth, c1.q64, order, true, st));
+                TRY(read_norms(P, st));
+                rel_prev = cycles == 2 ? 1.0 : rel;
+                rel = std::sqrt(P->hnorm[1]) / r0;
+                trace_point(P, order, cycles - 1, cycles - 1, rel);
+                bool stop = true;
+                if (!std::isfinite(rel)) { set_error("non-finite residual after %d cycles", cycles - 1); status = DMGS_ERR_NONFINITE; }
+                else if (rel <= o.rtol) { }
+                else if (cycles - 1 >= o.max_cycles) { set_error("not converged after %d cycles (rel %.3e)", cycles - 1, rel); status = DMGS_ERR_NOT_CONVERGED; }
+                else stop = false;
+                if (stop) {
+                    // the result is the cycle's input, which its first sweeps only read
+                    cur = prev;
+                    cycles--;
+                    break;
+                }
+                // this cycle's iterate: the last one, if its contraction is the last cycle's
+                P->epi_fused = want_epi && rel < rel_prev && rel * (rel / rel_prev) <= 4.0 * o.rtol;
+                TRY(post_grid_blocks(P, &cur, &oth, b, ccur, order, st, P->epi_fused));
+                continue;
+            }
+            if (blocks) {
+                done = want_epi && (fixed ? cycles == nfix : epi_next);
+                TRY(vcycle_grid_blocks(P, 0, &cur, &oth, b, order, false, st, done));
+            } else TRY(vcycle_grid(P, 0, x, b, order, st, want_epi && (fixed ? cycles == nfix : epi_next), &done));
             P->epi_fused = done;
+            if (free_norm) continue;   // the norm of this iterate comes with the next cycle
             if (fixed) {
                 if (P->cfg_trace) {
                     TRY(resid_grid(P, x, b, 1, st));
@@ -1612,6 +1772,7 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
     } else {
         cycles = 0;
     }
+    if (cur != x) HIPCHK(hipMemcpyAsync(x, cur, l0.nv * sizeof(double), hipMemcpyDeviceToDevice, st));
     if (fixed && info) {
         TRY(resid_grid(P, x, b, 1, st));
         TRY(read_norms(P, st));
@@ -1687,15 +1848,19 @@ int solve(dmgs_plan P, const double* b, double* x, double bc, int order, dmgs_in
         // pass's input buffer) is returned and the rest of that cycle is
         // dropped.
         SweepArgs<double> probe;
-        const bool free_norm = !fixed && !want_epi && !wjacobi(P) && P->L > 1 && fused_level(P, 0) &&
-                               use_sweep2(P, 0, sizeof(double)) && nu_pre_of(P, order) >= 2 &&
-                               nu_post_of(P, order) >= 1 && sweep2_grid<double>(P, probe, l0.N, kSweep2TY, kSweep2TZ64) <= kMaxPartials;
+        const bool blocks = block_level<double>(P, 0);
+        const bool free_norm = !fixed && !want_epi && !wjacobi(P) && P->L > 1 &&
+                               (blocks ? block_sweep_blocks(P, 0) <= kMaxPartials
+                                       : fused_level(P, 0) && use_sweep2(P, 0, sizeof(double)) && nu_pre_of(P, order) >= 2 &&
+                                             nu_post_of(P, order) >= 1 &&
+                                             sweep2_grid<double>(P, probe, l0.N, kSweep2TY, kSweep2TZ64) <= kMaxPartials);
         for (cycles = 1; !(fixed && nfix == 0); cycles++) {
             if (free_norm && cycles >= 2) {
                 // cycle `cycles` from u_{cycles-1} (in cur)
                 double* prev = cur;
                 unsigned nb = 0;
-                TRY(smooth_pass2<double>(P, 0, cur, oth, b, order, false, nullptr, st, nullptr, P->partial, &nb));
+                if (blocks) TRY(block_launch<double>(P, 0, kB3Sweep, cur, oth, b, nullptr, nullptr, order, st, P->partial, &nb));
+                else TRY(smooth_pass2<double>(P, 0, cur, oth, b, order, false, nullptr, st, nullptr, P->partial, &nb));
                 std::swap(cur, oth);
                 hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial, (int)nb,
                                    norm_dst(P), 1);
@@ -1704,7 +1869,8 @@ int solve(dmgs_plan P, const double* b, double* x, double bc, int order, dmgs_in
                 if (nu_pre_of(P, order) > 2)
                     TRY(smooth_phase<double>(P, 0, &cur, &oth, b, nu_pre_of(P, order) - 2, order, false, (const double*)nullptr, st));
                 const Level& c1 = P->lev[1];
-                TRY(defect_restrict<double>(P, 0, cur, b, c1.q64, st));
+                if (blocks) TRY(block_launch<double>(P, 0, kB3Defect, cur, nullptr, b, nullptr, c1.q64, order, st));
+                else TRY(defect_restrict<double>(P, 0, cur, b, c1.q64, st));
                 double* ccur = c1.u64;
                 double* coth = c1.t64;
                 TRY(vcycle<double>(P, 1, &ccur, &coth, c1.q64, order, true, st));
@@ -1776,7 +1942,8 @@ int solve(dmgs_plan P, const double* b, double* x, double bc, int order, dmgs_in
         // discards it.  With ir_adaptive, a step after the first runs the
         // number of V-cycles the per-cycle contraction factor observed so
         // far predicts the tolerance needs (at most ir_inner_cycles).
-        const bool can_speculate = !fixed && !wjacobi(P) && P->L > 1 && fused_level(P, 0) && !block_level<float>(P, 0);
+        const bool spec_blocks = block_level<float>(P, 0);
+        const bool can_speculate = !fixed && !wjacobi(P) && P->L > 1 && (spec_blocks || fused_level(P, 0));
         const bool adaptive = !fixed && o.ir_adaptive;
         double rel1 = 1.0;     // relative residual before the last step
         double rate = 0.0;     // per-V-cycle contraction factor (0: not known yet)
@@ -1796,8 +1963,9 @@ int solve(dmgs_plan P, const double* b, double* x, double bc, int order, dmgs_in
                 // residual the last step is expected to reach
                 const double pred = cycles == 0 ? 1.0 : rel1 * std::pow(rate > 0.0 ? rate : 0.5, inner);
                 if (can_speculate && cycles < o.max_cycles && pred > o.rtol) {
-                    TRY(smooth_phase<float>(P, 0, &e, &eo, l0.q32, nu_pre_of(P, order), order, true, (const float*)nullptr, st,
-                                            l0.r32, &rdone));
+                    if (spec_blocks) TRY(block_pre<float>(P, 0, &e, &eo, l0.q32, P->lev[1].q32, order, true, st));
+                    else TRY(smooth_phase<float>(P, 0, &e, &eo, l0.q32, nu_pre_of(P, order), order, true, (const float*)nullptr, st,
+                                                 l0.r32, &rdone));
                     smoothed = true;
                 }
                 TRY(read_norms(P, st));
@@ -2373,6 +2541,12 @@ int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
         if (k > 0 && st == DMGS_OK) st = dalloc(P, &l.u64, l.nv);
         if (k > 0 && st == DMGS_OK) st = dalloc(P, &l.q64, l.nv);
         if (k < P->L - 1 && st == DMGS_OK) st = dalloc(P, &l.t64, l.nv);
+    }
+    // first level handled by the single-workgroup kernel, if any
+    for (int k = 1; k < P->L && P->small64 < 0; k++) {
+        int nc[kSmallMaxLevels][3];
+        const int nl = small_counts(P, k, nc);
+        if (small_fits(nc, nl)) P->small64 = k;
     }
     if (st == DMGS_OK) st = dalloc(P, &P->scratch64, P->lev[0].nv);
     if (st == DMGS_OK) st = dalloc(P, &P->partial, kMaxPartials);

@@ -7,9 +7,10 @@
 // z fastest.  The operator is the 7-point stencil of Eq. (maineq) with the
 // face coefficient of each axis scaled by that axis's 1/h^2; smoothing,
 // transfers, coarsening, the exact coarsest solve and the derivative
-// kernels follow the cubic kernels axis by axis.  These grids are small
-// (the paper's has 0.55 M vertices), so the kernels are written for
-// clarity rather than streamed.
+// kernels follow the cubic kernels axis by axis.  V(2,2) cycles run in
+// register blocks (kernels_block.hpp) and the coarse kernel instead of the
+// half-sweep, defect, transfer and exact-solve kernels here, which serve
+// other smoothing counts and the levels those do not take.
 #pragma once
 #include "kernels_basic.hpp"
 

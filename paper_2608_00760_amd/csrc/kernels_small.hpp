@@ -11,14 +11,9 @@
 // of about 50 instructions, 400 cycles) and every other step by the latency
 // of an LDS read.  Three choices keep the steps few and short:
 //
-//  - A thread owns a block of 2 x 2 x 2 vertices (even corner) and keeps
-//    their iterate, right-hand side, inverse diagonal and all 36 face
-//    coefficients in registers.  Half of every vertex's neighbours are then
-//    the thread's own; the others are read from LDS, three per update, where
-//    the iterate lies by octant (position in the block) so that the lanes of
-//    a wave read consecutive words.  A half-sweep is 12 LDS reads, 28
-//    multiply-adds and a barrier.  (With D, w and q read from LDS as well,
-//    two vertices a thread, a half-sweep took three times as long.)
+//  - A thread owns a block of 2 x 2 x 2 vertices (Block3).  A half-sweep is
+//    12 LDS reads, 28 multiply-adds and a barrier.  (With D, w and q read
+//    from LDS as well, two vertices a thread, it took three times as long.)
 //  - A coarse vertex 2X is the corner of block X, so the thread that owns the
 //    block also restricts to X and prolongs from X .. X+1: no other index map.
 //  - Every level below the first has at most 64 blocks and belongs to one
@@ -36,6 +31,7 @@
 #pragma once
 #include "grid.hpp"
 #include "kernels_basic.hpp"
+#include "kernels_block.hpp"
 
 namespace dmgs {
 
@@ -125,7 +121,8 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
     const int sb = ml == 0 ? 3 : 2, mb = (1 << sb) - 1;
     const int bz = tid & mb, by = (tid >> sb) & mb, bx = (tid >> (2 * sb)) & mb;
     const bool act = mine && bx < nb0 && by < nb1 && bz < nb2;
-    constexpr int S = kSmallS, stepB[3] = {kSmallX, kSmallY, 1};         // to the next octant; block per axis
+    using B3 = Block3<T, kSmallS, kSmallX, kSmallY>;
+    constexpr int S = kSmallS;
     const int idx = small_off(ml) + bx * kSmallX + by * kSmallY + bz;     // own octant o: base[idx + o S]
     // the coarsest operator's inverse (transposed)
     double* const sinv = reinterpret_cast<double*>(small_smem + kSmallWords * sizeof(T));
@@ -142,12 +139,7 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
         return;
     }
 
-    // state of the block: octant o has bit 2 for x, 1 for y, 0 for z
-    T u[8], q[8], w[8];
-    T ci[3][4];    // faces inside the block per axis, by the other two bits
-    T co[3][8];    // faces to the neighbouring blocks, by octant
-    auto inner = [](int ax, int o) { return ax == 0 ? o & 3 : ax == 1 ? (o >> 2) * 2 + (o & 1) : o >> 1; };
-    constexpr int bitOf[3] = {4, 2, 1};
+    B3 P;   // the block's state
 
     // own D, w and q; own D and the D past the end of each axis to the
     // octants, the neighbours' D from them; the coarsest inverse
@@ -171,13 +163,13 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
             }
         };
         load(lv.D, act, T(1), D);
-        load(lv.w, act, T(0), w);
-        load(a.q, act && ml == 0, T(0), q);
+        load(lv.w, act, T(0), P.w);
+        load(a.q, act && ml == 0, T(0), P.q);
 #pragma unroll
         for (int ax = 0; ax < 3; ax++)
 #pragma unroll
             for (int o = 0; o < 8; o++)
-                if (o & bitOf[ax]) De[ax][inner(ax, o)] = edge[ax] ? lv.D[vert(o) + ev[ax]] : T(0);
+                if (o & B3::bit(ax)) De[ax][B3::inner(ax, o)] = edge[ax] ? lv.D[vert(o) + ev[ax]] : T(0);
         for (int i = tid; i < kSmallWords; i += kSmallThreads) base[i] = T(0);
         for (int i = tid; i < m * m; i += kSmallThreads) sinv[(i % m) * m + i / m] = a.cinv[i];
         __syncthreads();
@@ -185,34 +177,19 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
         for (int ax = 0; ax < 3; ax++)
 #pragma unroll
             for (int o = 0; o < 8; o++)
-                if ((o & bitOf[ax]) && edge[ax]) base[idx + (o ^ bitOf[ax]) * S + stepB[ax]] = De[ax][inner(ax, o)];
+                if ((o & B3::bit(ax)) && edge[ax]) base[idx + B3::outer(ax, o)] = De[ax][B3::inner(ax, o)];
         // the D of the low y and z faces is nobody's neighbour but boundary
         // vertices' (their entries may be an edge's)
 #pragma unroll
         for (int o = 0; o < 8; o++)
             if (act && (by > 0 || (o & 2)) && (bz > 0 || (o & 1))) base[idx + o * S] = D[o];
         __syncthreads();
-        auto fc = [&](int ax, T Da, T Db) -> T {
-            if (HARM) return (Da * Db) / (Da + Db) * lv.s[ax];
-            return (Da + Db) * lv.s[ax];
-        };
-#pragma unroll
-        for (int ax = 0; ax < 3; ax++)
-#pragma unroll
-            for (int o = 0; o < 8; o++) {
-                const int p = o ^ bitOf[ax];
-                const int j = idx + p * S + ((o & bitOf[ax]) ? stepB[ax] : -stepB[ax]);
-                co[ax][o] = fc(ax, D[o], act ? base[j] : T(0));
-                if (!(o & bitOf[ax])) ci[ax][inner(ax, o)] = fc(ax, D[o], D[p]);
-            }
+        P.template coefs<HARM>(base, idx, D, lv.s);
         if (a.from_mu) {
 #pragma unroll
             for (int o = 0; o < 8; o++) {
-                T d = w[o];
-#pragma unroll
-                for (int ax = 0; ax < 3; ax++) d += ci[ax][inner(ax, o)] + co[ax][o];
-                const bool in = (bx > 0 || (o & 4)) && (by > 0 || (o & 2)) && (bz > 0 || (o & 1));
-                w[o] = in && act ? T(1) / d : T(0);
+                const bool in = act && (bx > 0 || (o & 4)) && (by > 0 || (o & 2)) && (bz > 0 || (o & 1));
+                P.w[o] = in ? T(1) / P.diag(o, P.w[o]) : T(0);
             }
         }
     }
@@ -222,49 +199,11 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
     for (int ax = 0; ax < 3; ax++)
 #pragma unroll
         for (int o = 0; o < 8; o++)
-            if ((o & bitOf[ax]) && edge[ax]) base[idx + (o ^ bitOf[ax]) * S + stepB[ax]] = T(0);
+            if ((o & B3::bit(ax)) && edge[ax]) base[idx + B3::outer(ax, o)] = T(0);
 
-    // q + sum_j c_ij u_j at the octants of one colour (the Gauss-Seidel value
-    // is w times it); a colour's octants have one bit parity (the corner's
-    // coordinates are even).  All LDS reads are issued before the first is
-    // used: left to itself the compiler interleaves them with the sums and
-    // waits for the LDS four times over.
-    auto numer = [&](auto Cc, T* s) {
-        constexpr int C = decltype(Cc)::value;
-        T nb[8][3];
-#pragma unroll
-        for (int o = 0; o < 8; o++)
-            if ((__builtin_popcount(o) & 1) == C)
-#pragma unroll
-                for (int ax = 0; ax < 3; ax++)
-                    nb[o][ax] = base[idx + (o ^ bitOf[ax]) * S + ((o & bitOf[ax]) ? stepB[ax] : -stepB[ax])];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int o = 0; o < 8; o++)
-            if ((__builtin_popcount(o) & 1) == C) {
-                s[o] = q[o];
-#pragma unroll
-                for (int ax = 0; ax < 3; ax++) s[o] += ci[ax][inner(ax, o)] * u[o ^ bitOf[ax]];
-#pragma unroll
-                for (int ax = 0; ax < 3; ax++) s[o] += co[ax][o] * nb[o][ax];
-            }
-    };
-    auto half = [&](auto Cc) {
-        constexpr int C = decltype(Cc)::value;
-        T v[8];
-        numer(Cc, v);
-#pragma unroll
-        for (int o = 0; o < 8; o++)
-            if ((__builtin_popcount(o) & 1) == C) {
-                u[o] = v[o] * w[o];
-                base[idx + o * S] = u[o];
-            }
-    };
-    using C0 = std::integral_constant<int, 0>;
-    using C1 = std::integral_constant<int, 1>;
     auto half_of = [&](int c) {
-        if (c) half(C1());
-        else half(C0());
+        if (c) P.template half<1, false>(base, idx);
+        else P.template half<0, false>(base, idx);
     };
     // level 0 is shared by waves 0 .. 7: its steps end with a workgroup
     // barrier, which every wave joins; the other levels are one wave's
@@ -288,69 +227,34 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
             // the first colour
 #pragma unroll
             for (int o = 0; o < 8; o++) {
-                if (l > 0) q[o] = base[idx + o * S];
-                u[o] = (a.nu_pre > 0 && (__builtin_popcount(o) & 1) == first) ? w[o] * q[o] : T(0);
+                if (l > 0) P.q[o] = base[idx + o * S];
+                P.u[o] = (a.nu_pre > 0 && B3::colour(o) == first) ? P.w[o] * P.q[o] : T(0);
             }
-#pragma unroll
-            for (int o = 0; o < 8; o++) base[idx + o * S] = u[o];
+            B3::publish(base, idx, P.u);
         }
         sync(l);
         sweeps(l, a.nu_pre, true);
         // defect of the first colour, 0 for the other (of both when nothing
         // was smoothed: there it is q), 0 on the boundary (w = 0)
-        auto defect = [&](auto Cc) {
-            constexpr int C = decltype(Cc)::value;
-            T r[8] = {};
-            if (run) {
-                numer(Cc, r);
+        T r[8] = {};
+        if (run) {
+            if (a.nu_pre == 0) {
 #pragma unroll
-                for (int o = 0; o < 8; o++)
-                    if ((__builtin_popcount(o) & 1) == C) r[o] = w[o] == T(0) ? T(0) : r[o] - u[o] / w[o];
+                for (int o = 0; o < 8; o++) r[o] = P.w[o] == T(0) ? T(0) : P.q[o];
+            } else if (first) {
+                P.template residual<1>(base, idx, r);
+            } else {
+                P.template residual<0>(base, idx, r);
             }
-            sync(l);
-            if (run) {
-#pragma unroll
-                for (int o = 0; o < 8; o++) base[idx + o * S] = r[o];
-            }
-        };
-        if (a.nu_pre == 0) {
-            sync(l);
-            if (run) {
-#pragma unroll
-                for (int o = 0; o < 8; o++) base[idx + o * S] = w[o] == T(0) ? T(0) : q[o];
-            }
-        } else if (first) {
-            defect(C1());
-        } else {
-            defect(C0());
         }
+        sync(l);
+        if (run) B3::publish(base, idx, r);
         sync(l);
         // restriction to the corner X = (bx, by, bz), interior: octant o
         // of block X and, where its bit is set, of the block before
         if (run && bx > 0 && by > 0 && bz > 0) {
-            auto sum = [&](auto Cc) -> T {   // over the octants of one colour
-                constexpr int C = decltype(Cc)::value;
-                T v[8][8], s = T(0);
-#pragma unroll
-                for (int o = 0; o < 8; o++)
-#pragma unroll
-                    for (int k = 0; k < 8; k++)
-                        if ((__builtin_popcount(o) & 1) == C && !(k & ~o))
-                            v[o][k] = base[idx + o * S - ((k & 4) ? stepB[0] : 0) - ((k & 2) ? stepB[1] : 0) -
-                                           ((k & 1) ? stepB[2] : 0)];
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int o = 0; o < 8; o++) {
-                    T t = T(0);
-#pragma unroll
-                    for (int k = 0; k < 8; k++)
-                        if ((__builtin_popcount(o) & 1) == C && !(k & ~o)) t += v[o][k];
-                    if ((__builtin_popcount(o) & 1) == C) s += t * T(8 >> __builtin_popcount(o));
-                }
-                return s;
-            };
-            T s = first ? sum(C1()) : sum(C0());
-            if (a.nu_pre == 0) s += first ? sum(C0()) : sum(C1());
+            T s = first ? B3::template weighted<1>(base, idx) : B3::template weighted<0>(base, idx);
+            if (a.nu_pre == 0) s += first ? B3::template weighted<0>(base, idx) : B3::template weighted<1>(base, idx);
             base[small_at(small_off(l + 1), bx, by, bz)] = s * T(1.0 / 64.0);
         }
         __syncthreads();
@@ -372,15 +276,9 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
 #pragma unroll
             for (int o = 0; o < 8; o++) E[o] = base[small_at(small_off(l + 1), bx + (o >> 2), by + ((o >> 1) & 1), bz + (o & 1))];
 #pragma unroll
-            for (int o = 0; o < 8; o++) {
-                T s = T(0);
-#pragma unroll
-                for (int k = 0; k < 8; k++)
-                    if (!(k & ~o)) s += E[k];
-                if (w[o] != T(0)) u[o] += s * T(1.0 / (1 << __builtin_popcount(o)));
-            }
-#pragma unroll
-            for (int o = 0; o < 8; o++) base[idx + o * S] = u[o];
+            for (int o = 0; o < 8; o++)
+                if (P.w[o] != T(0)) P.u[o] += B3::corrected(E, o);
+            B3::publish(base, idx, P.u);
         }
         sync(l);
         sweeps(l, a.nu_post, false);
@@ -389,7 +287,7 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
     if (ml == 0 && act) {
 #pragma unroll
         for (int o = 0; o < 8; o++)
-            if (w[o] != T(0)) a.u[vert(o)] = u[o];   // boundary entries stay 0
+            if (P.w[o] != T(0)) a.u[vert(o)] = P.u[o];   // boundary entries stay 0
     }
 }
 

@@ -1,0 +1,78 @@
+"""Register-block smoothing passes at the edges of their tiles.
+
+Cubic grids of one tile, of several with a ragged last one, and general grids
+whose axes end inside a tile, at a tile's end and below one tile, each
+through fixed-cycle solves and their pull-backs against the oracles (1e-12 of
+the largest entry: rounding order only), with a boundary value and both face
+means; and the residual norm that the next cycle's first sweeps leave against
+the oracle operator's residual of the returned iterate (1e-3 of it, as for
+the marching passes: a norm of the wrong iterate or colour is off by a factor
+of two and more).
+"""
+import numpy as np
+import pytest
+
+from gpu_util import dev, host, rel_max, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N", [4, 8, 24, 48, 64])
+@pytest.mark.parametrize("face_mean,g", [("arith", 0.0), ("harmonic", 0.3)])
+def test_blocks_cubic_fp64(N, face_mean, g):
+    from oracle import ref
+    from paper_2608_00760_amd import synth
+    from paper_2608_00760_amd.solver import Options, Plan
+    say("blocks cubic N=%d %s g=%g" % (N, face_mean, g))
+    c = synth.grf_case(N, 1200 + N)
+    H = ref.Hierarchy(c["D"], c["mua"], face_mean=face_mean, bc=g)
+    P = Plan(Options(N, fixed_cycles=2, face_mean=face_mean, bc_value=g))
+    P.set_coefficients(dev(c["D"]), dev(c["mua"]))
+    rho, _ = P.forward(dev(c["q"]))
+    rr, _ = H.forward(c["q"], fixed_cycles=2)
+    assert rel_max(host(rho), rr) <= 1e-12
+    (qb, gD, gmu), _ = P.vjp(rho, dev(c["rhobar"]))
+    for a, b in zip((qb, gD, gmu), H.vjp(rr, c["rhobar"], fixed_cycles=2)[0]):
+        assert rel_max(host(a), b) <= 1e-12
+    P.close()
+
+
+@pytest.mark.parametrize("cells", [(16, 40, 24), (8, 20, 12), (56, 16, 24), (12, 12, 4), (6, 10, 4), (80, 32, 112)])
+@pytest.mark.parametrize("face_mean,g", [("arith", 0.2), ("harmonic", 0.0)])
+def test_blocks_general_grid(cells, face_mean, g):
+    from oracle import refgrid
+    from paper_2608_00760_amd import synth
+    from paper_2608_00760_amd.solver import Options, Plan
+    say("blocks grid", cells, face_mean, "g=%g" % g)
+    h = (0.7, 1.1, 0.9)
+    c = synth.grid_case(cells, 1300 + cells[0])
+    H = refgrid.HierarchyGrid(c["D"], c["mua"], h=h, face_mean=face_mean, g=g)
+    P = Plan(Options(cells[0], shape=cells, spacing=h, fixed_cycles=2, face_mean=face_mean, bc_value=g))
+    P.set_coefficients(dev(c["D"]), dev(c["mua"]))
+    rho, _ = P.forward(dev(c["q"]))
+    rr, _ = H.forward(c["q"], fixed_cycles=2)
+    assert rel_max(host(rho), rr) <= 1e-12
+    (qb, gD, gmu), _ = P.vjp(rho, dev(c["rhobar"]))
+    for a, b in zip((qb, gD, gmu), H.vjp(rr, c["rhobar"], fixed_cycles=2)[0]):
+        assert rel_max(host(a), b) <= 1e-12
+    P.close()
+
+
+@pytest.mark.parametrize("cells", [(32, 32, 32), (48, 24, 32)])
+def test_norm_from_the_next_sweeps(cells):
+    from oracle import refgrid
+    from paper_2608_00760_amd import synth
+    from paper_2608_00760_amd.solver import Options, Plan
+    say("norm from the next sweeps", cells)
+    c = synth.grid_case(cells, 1400 + cells[1])
+    H = refgrid.HierarchyGrid(c["D"], c["mua"])
+    P = Plan(Options(cells[0], shape=cells))
+    P.set_coefficients(dev(c["D"]), dev(c["mua"]))
+    for solve, b in ((lambda q: P.forward(q), c["q"]), (lambda q: (lambda r: (r[0][0], r[1]))(P.vjp(q, q, coef_grads=False)), c["rhobar"])):
+        x, info = solve(dev(b))
+        r = H.defect(0, host(x), b)
+        z = np.zeros_like(b)
+        rel = np.linalg.norm(r) / np.linalg.norm(H.defect(0, z, b))
+        assert info["rel_residual"] <= 1e-10
+        assert abs(rel - info["rel_residual"]) <= 1e-3 * info["rel_residual"]
+    P.close()
