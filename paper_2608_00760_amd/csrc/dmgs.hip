@@ -237,7 +237,57 @@ int64_t nv32_of(const dmgs_options* o, const Sizes& s, int k, int py0) {
     return n * n * py0;
 }
 
-size_t footprint(const dmgs_options* o) {
+// Levels k .. L-1 of the plan as cells per axis, for small_fits.
+int small_counts(dmgs_plan P, int k, int (*nc)[3]) {
+    const int nl = P->L - k;
+    if (nl > kSmallMaxLevels) return 0;
+    for (int i = 0; i < nl; i++)
+        for (int a = 0; a < 3; a++) nc[i][a] = P->lev[k + i].nc[a];
+    return nl;
+}
+
+// Interior vertices of level k.
+int64_t unknowns(const Level& l) { return (int64_t)(l.nc[0] - 1) * (l.nc[1] - 1) * (l.nc[2] - 1); }
+
+// The coarse kernel's first level, and the first of its levels whose whole
+// cycle is one product with a matrix (small enough for the kernel, and above
+// the coarsest).
+void choose_small_levels(dmgs_plan P) {
+    P->small32 = P->small64 = P->tail_level = -1;
+    for (int k = 1; k < P->L; k++) {
+        int nc[kSmallMaxLevels][3];
+        const int nl = small_counts(P, k, nc);
+        if (!small_fits(nc, nl)) continue;
+        P->small32 = P->small64 = k;
+        for (int t = k; t < P->L - 1 && P->tail_level < 0; t++)
+            if (unknowns(P->lev[t]) <= kSmallCoarseMax) P->tail_level = t;
+        return;
+    }
+}
+
+// Entries of the coarse cycle's matrix (choose_small_levels on the options).
+int64_t tail_entries(const dmgs_options* o) {
+    if (o->ndim == 2) return 0;
+    dmgs_plan_s P;   // level counts only
+    if (general_grid(o)) {
+        int cn[kMaxLevels][3];
+        P.L = grid_levels(o->n, cn);
+        for (int k = 0; k < P.L; k++)
+            for (int a = 0; a < 3; a++) P.lev[k].nc[a] = cn[k][a];
+    } else {
+        P.L = levels_for(o->n[0]);
+        for (int k = 0; k < P.L; k++)
+            for (int a = 0; a < 3; a++) P.lev[k].nc[a] = o->n[0] >> k;
+    }
+    choose_small_levels(&P);
+    if (P.tail_level < 0) return 0;
+    const int64_t m = unknowns(P.lev[P.tail_level]);
+    return m * m;
+}
+
+// arena: without the coarse cycle's matrix and the second flag word (at most
+// 33 KB), which the slack of an arena plan holds.
+size_t footprint(const dmgs_options* o, bool arena = false) {
     Sizes s = sizes_for(o);
     bool ir = o->precision == DMGS_FP32_IN_FP64;
     size_t b = 0;
@@ -249,8 +299,8 @@ size_t footprint(const dmgs_options* o) {
             b += (2 + (k > 0 ? 2 : 0) + (k < s.L - 1 ? 1 : 0)) * s.nv[k] * sizeof(double);
         b += s.nv[0] * sizeof(double);
         b += kMaxPartials * sizeof(double) + kGridCoarseMax * kGridCoarseMax * sizeof(double) + 4 * sizeof(double) +
-             sizeof(int);
-        return b;
+             (arena ? 1 : 2) * sizeof(int);
+        return b + (arena ? 0 : tail_entries(o) * sizeof(double));
     }
     const int py0 = fine_row_pitch(o, read_knobs(o), s.L);
     for (int k = 0; k < s.L; k++) {
@@ -263,12 +313,15 @@ size_t footprint(const dmgs_options* o) {
         else b += (k > 0 ? 4 : 2) * s.nv[k] * sizeof(double);         // w64, (u64, q64), t64
     }
     b += (ir ? 2 : 1) * s.nv[0] * sizeof(double);                     // scratch64 (+ xalt64)
-    b += kMaxPartials * sizeof(double) + kCoarseMax * kCoarseMax * sizeof(double) + 4 * sizeof(double) + sizeof(int);
-    return b;
+    b += kMaxPartials * sizeof(double) + kCoarseMax * kCoarseMax * sizeof(double) + 4 * sizeof(double) +
+         (arena ? 1 : 2) * sizeof(int);
+    return b + (arena ? 0 : tail_entries(o) * sizeof(double));
 }
 
 // Slack of an arena plan over its footprint: each buffer starts on a 256-byte
-// boundary (at most kMaxLevels * 12 + 8 buffers).
+// boundary (at most 10 levels of 12 buffers and 8 more for cubic plans, whose
+// coarse cycle's matrix takes 6 KB; 10 levels of 5 and 6 more for general
+// grids, whose matrix takes at most 32 KB).
 constexpr size_t kArenaSlack = 64 * 1024;
 
 template <class T>
@@ -319,6 +372,7 @@ void free_plan(dmgs_plan P) {
     if (P->xalt64) (void)hipFree(P->xalt64);
     if (P->partial) (void)hipFree(P->partial);
     if (P->cinv && P->owns_coef) (void)hipFree(P->cinv);
+    if (P->ctail && P->owns_coef) (void)hipFree(P->ctail);
     if (P->dflag) (void)hipFree(P->dflag);
     if (P->hnorm) (void)hipHostFree(P->hnorm);
     if (P->hflag) (void)hipHostFree(P->hflag);
@@ -847,6 +901,64 @@ int coarsest(dmgs_plan P, const T* q, T* u, hipStream_t st) {
 
 bool fused_level(dmgs_plan P, int k) { return P->lev[k].N >= P->cfg_fuse_min && k < P->L - 1; }
 
+// Smoothing counts of a cycle: the transposed cycle (order 1) reverses the
+// cycle's steps, so it pre-smooths with the forward cycle's post-smoothing
+// count and post-smooths with its pre-smoothing count.
+int nu_pre_of(dmgs_plan P, int order) { return order ? P->opt.nu_post : P->opt.nu_pre; }
+int nu_post_of(dmgs_plan P, int order) { return order ? P->opt.nu_pre : P->opt.nu_post; }
+
+template <class T>
+int small_level(dmgs_plan P) { return sizeof(T) == 4 ? P->small32 : P->small64; }
+
+// Arguments of the coarse kernel from level k: down to the matrix level, or
+// (to_coarsest) the coarsest.
+template <class T, bool HARM>
+int small_args(dmgs_plan P, int k, const T* q, T* u, int order, SmallArgs<T>& a, bool to_coarsest = false) {
+    const bool tail = P->tail_level >= 0 && !to_coarsest;
+    int nc[kSmallMaxLevels][3];
+    a.nlev = small_counts(P, k, nc);
+    if (!small_fits(nc, a.nlev)) {
+        set_error("internal: levels from %d do not fit the coarse kernel", k);
+        return DMGS_ERR_INVALID;
+    }
+    if (tail) a.nlev = P->tail_level - k + 1;
+    for (int i = 0; i < a.nlev; i++) {
+        const Level& l = P->lev[k + i];
+        for (int x = 0; x < 3; x++) {
+            a.lev[i].nc[x] = nc[i][x];
+            a.lev[i].s[x] = (T)((HARM ? 2.0 : 0.5) / (l.h3[x] * l.h3[x]));
+        }
+        a.lev[i].D = Typed<T>::D(l);
+        a.lev[i].w = P->grid ? Typed<T>::mu(l) : Typed<T>::w(l);
+    }
+    a.q = q;
+    a.u = u;
+    a.cinv = tail ? P->ctail : P->cinv;
+    a.ctrans = tail ? order : 0;
+    a.nu_pre = nu_pre_of(P, order);
+    a.nu_post = nu_post_of(P, order);
+    a.order = order;
+    a.from_mu = P->grid ? 1 : 0;
+    return DMGS_OK;
+}
+
+// The matrix of the cycle from the plan's tail level down (once per
+// coefficient set).
+template <class T, bool HARM>
+int build_tail(dmgs_plan P, hipStream_t st) {
+    SmallArgs<T> a;
+    TRY((small_args<T, HARM>(P, P->tail_level, nullptr, nullptr, 0, a, true)));
+    hipLaunchKernelGGL((k_small_cols<T, HARM>), dim3((unsigned)unknowns(P->lev[P->tail_level])), dim3(kSmallThreads),
+                       small_lds_bytes<T>(), st, a, P->ctail);
+    LAUNCHCHK();
+    return DMGS_OK;
+}
+template <class T>
+int build_tail(dmgs_plan P, hipStream_t st) {
+    if (P->tail_level < 0) return DMGS_OK;
+    return harmonic(P) ? build_tail<T, true>(P, st) : build_tail<T, false>(P, st);
+}
+
 // Mid-size levels run each smoothing phase as one launch of register blocks
 // (two sweeps each way).  Float32: the refinement corrections above the
 // coarse kernel's levels.  Float64: every cubic level up to the same size,
@@ -857,6 +969,25 @@ bool block_level(dmgs_plan P, int k) {
     if (P->grid) return sizeof(T) == 8;
     const int N = P->lev[k].N;
     return (sizeof(T) == 4) == is_ir(P) && N <= P->cfg_block_max && (N > 16 || (sizeof(T) == 8 && k == 0 && N >= 4));
+}
+
+// A block level whose pre-smoothing restricts straight to the coarse kernel's
+// first level: that launch runs the coarse kernel as its last workgroup, and
+// the coarse level's u holds the correction when it ends.
+template <class T>
+bool coarse_behind(dmgs_plan P, int k) { return block_level<T>(P, k) && small_level<T>(P) == k + 1; }
+
+template <class T, int MODE, bool HARM, bool GEN>
+int launch_block_tail(dmgs_plan P, int k, const Block3Args<T>& b, unsigned nb, hipStream_t st) {
+    BlockTailArgs<T> a;
+    a.b = b;
+    TRY((small_args<T, HARM>(P, k + 1, b.qc, Typed<T>::u(P->lev[k + 1]), b.order, a.s)));
+    a.done = reinterpret_cast<unsigned*>(P->dflag + 1);
+    a.nb = (int)nb;
+    const void* grp = nullptr;
+    if constexpr (sizeof(T) == 4) grp = (const void*)k_block_tail_grp<T, MODE, HARM>;
+    return launch_rec(P, (const void*)k_block_tail<T, MODE, HARM, GEN>, grp, nb + 1, block_tail_threads<MODE, GEN>(),
+                      block_tail_lds<T, MODE, GEN>(), a, st);
 }
 
 template <class T, int MODE, bool HARM>
@@ -870,6 +1001,16 @@ int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st, unsigned
         nb *= (unsigned)a.nt[x];
     }
     if (nb_out) *nb_out = nb;
+    if constexpr (MODE == kB3PreZero || MODE == kB3Pre || MODE == kB3Defect) {
+        if (coarse_behind<T>(P, k)) {
+            if constexpr (sizeof(T) == 8)
+                if (P->grid) {
+                    a.w = Typed<T>::mu(l);
+                    return launch_block_tail<T, MODE, HARM, true>(P, k, a, nb, st);
+                }
+            return launch_block_tail<T, MODE, HARM, false>(P, k, a, nb, st);
+        }
+    }
     if constexpr (MODE == kB3PostEpi) {
         a.w = l.mu64;
         hipLaunchKernelGGL((k_block3<T, MODE, HARM, true>), dim3(nb), dim3(Block3Shape<MODE, true>::NT),
@@ -982,7 +1123,23 @@ int block_attributes() {
         {(const void*)k_block3<double, kB3PreZero, false, false>, block3_lds<double, kB3PreZero, false>()},
         {(const void*)k_block3<double, kB3PreZero, true, false>, block3_lds<double, kB3PreZero, false>()},
         {(const void*)k_block3<double, kB3PreZero, false, true>, block3_lds<double, kB3PreZero, true>()},
-        {(const void*)k_block3<double, kB3PreZero, true, true>, block3_lds<double, kB3PreZero, true>()}};
+        {(const void*)k_block3<double, kB3PreZero, true, true>, block3_lds<double, kB3PreZero, true>()},
+        {(const void*)k_block_tail<double, kB3PreZero, false, false>, block_tail_lds<double, kB3PreZero, false>()},
+        {(const void*)k_block_tail<double, kB3PreZero, true, false>, block_tail_lds<double, kB3PreZero, false>()},
+        {(const void*)k_block_tail<double, kB3PreZero, false, true>, block_tail_lds<double, kB3PreZero, true>()},
+        {(const void*)k_block_tail<double, kB3PreZero, true, true>, block_tail_lds<double, kB3PreZero, true>()},
+        {(const void*)k_block_tail<double, kB3Defect, false, false>, block_tail_lds<double, kB3Defect, false>()},
+        {(const void*)k_block_tail<double, kB3Defect, true, false>, block_tail_lds<double, kB3Defect, false>()},
+        {(const void*)k_block_tail<double, kB3Defect, false, true>, block_tail_lds<double, kB3Defect, true>()},
+        {(const void*)k_block_tail<double, kB3Defect, true, true>, block_tail_lds<double, kB3Defect, true>()},
+        {(const void*)k_block_tail<float, kB3PreZero, false, false>, block_tail_lds<float, kB3PreZero, false>()},
+        {(const void*)k_block_tail<float, kB3PreZero, true, false>, block_tail_lds<float, kB3PreZero, false>()},
+        {(const void*)k_block_tail<float, kB3Pre, false, false>, block_tail_lds<float, kB3Pre, false>()},
+        {(const void*)k_block_tail<float, kB3Pre, true, false>, block_tail_lds<float, kB3Pre, false>()},
+        {(const void*)k_block_tail_grp<float, kB3PreZero, false>, block_tail_lds<float, kB3PreZero, false>()},
+        {(const void*)k_block_tail_grp<float, kB3PreZero, true>, block_tail_lds<float, kB3PreZero, false>()},
+        {(const void*)k_block_tail_grp<float, kB3Pre, false>, block_tail_lds<float, kB3Pre, false>()},
+        {(const void*)k_block_tail_grp<float, kB3Pre, true>, block_tail_lds<float, kB3Pre, false>()}};
     for (const auto& f : fns)
         if (hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.second) != hipSuccess) {
             (void)hipGetLastError(); set_error("hipFuncSetAttribute failed");
@@ -990,12 +1147,6 @@ int block_attributes() {
         }
     return DMGS_OK;
 }
-
-// Smoothing counts of a cycle: the transposed cycle (order 1) reverses the
-// cycle's steps, so it pre-smooths with the forward cycle's post-smoothing
-// count and post-smooths with its pre-smoothing count.
-int nu_pre_of(dmgs_plan P, int order) { return order ? P->opt.nu_post : P->opt.nu_pre; }
-int nu_post_of(dmgs_plan P, int order) { return order ? P->opt.nu_pre : P->opt.nu_post; }
 
 // Pre-smoothing pass on level k: nu_pre_of sweeps from *cur (or from 0), then
 // qc = R (q - A u).  Simple levels work in place.
@@ -1032,47 +1183,14 @@ int post_pass(dmgs_plan P, int k, T** cur, T** other, const T* ec, const T* q, i
     return sweeps<T>(P, k, *cur, q, nu_post_of(P, order), order, st);
 }
 
-// Levels k .. L-1 of the plan as cells per axis, for small_fits.
-int small_counts(dmgs_plan P, int k, int (*nc)[3]) {
-    const int nl = P->L - k;
-    if (nl > kSmallMaxLevels) return 0;
-    for (int i = 0; i < nl; i++)
-        for (int a = 0; a < 3; a++) nc[i][a] = P->lev[k + i].nc[a];
-    return nl;
-}
-
 template <class T, bool HARM>
 int launch_small_t(dmgs_plan P, int k, const T* q, T* u, int order, hipStream_t st) {
     SmallArgs<T> a;
-    int nc[kSmallMaxLevels][3];
-    a.nlev = small_counts(P, k, nc);
-    if (!small_fits(nc, a.nlev)) {
-        set_error("internal: levels from %d do not fit the coarse kernel", k);
-        return DMGS_ERR_INVALID;
-    }
-    for (int i = 0; i < a.nlev; i++) {
-        const Level& l = P->lev[k + i];
-        for (int x = 0; x < 3; x++) {
-            a.lev[i].nc[x] = nc[i][x];
-            a.lev[i].s[x] = (T)((HARM ? 2.0 : 0.5) / (l.h3[x] * l.h3[x]));
-        }
-        a.lev[i].D = Typed<T>::D(l);
-        a.lev[i].w = P->grid ? Typed<T>::mu(l) : Typed<T>::w(l);
-    }
-    a.q = q;
-    a.u = u;
-    a.cinv = P->cinv;
-    a.nu_pre = nu_pre_of(P, order);
-    a.nu_post = nu_post_of(P, order);
-    a.order = order;
-    a.from_mu = P->grid ? 1 : 0;
+    TRY((small_args<T, HARM>(P, k, q, u, order, a)));
     const void* grp = nullptr;
     if constexpr (sizeof(T) == 4) grp = (const void*)k_small_grp<T, HARM>;
     return launch_rec(P, (const void*)k_small_vcycle<T, HARM>, grp, 1u, kSmallThreads, small_lds_bytes<T>(), a, st);
 }
-
-template <class T>
-int small_level(dmgs_plan P) { return sizeof(T) == 4 ? P->small32 : P->small64; }
 
 // --- weighted-Jacobi cycles -----------------------------------------------------
 
@@ -1146,7 +1264,7 @@ int vcycle(dmgs_plan P, int k, T** cur, T** other, const T* q, int order, bool z
     else TRY(pre_pass<T>(P, k, cur, other, q, qc, order, zero, st));
     T* ccur = Typed<T>::u(c);
     T* coth = Typed<T>::t(c);
-    TRY(vcycle<T>(P, k + 1, &ccur, &coth, qc, order, true, st));
+    if (!coarse_behind<T>(P, k)) TRY(vcycle<T>(P, k + 1, &ccur, &coth, qc, order, true, st));
     return post_pass<T>(P, k, cur, other, ccur, q, order, st);
 }
 
@@ -1645,7 +1763,7 @@ int vcycle_grid_blocks(dmgs_plan P, int k, double** cur, double** other, const d
     TRY(block_pre<double>(P, k, cur, other, q, c.q64, order, zero, st));
     double* ccur = c.u64;
     double* coth = c.t64;
-    TRY(vcycle_grid_blocks(P, k + 1, &ccur, &coth, c.q64, order, true, st));
+    if (!coarse_behind<double>(P, k)) TRY(vcycle_grid_blocks(P, k + 1, &ccur, &coth, c.q64, order, true, st));
     if (k == 0) return post_grid_blocks(P, cur, other, q, ccur, order, st, epi);
     return block_post<double>(P, k, cur, other, q, ccur, order, st);
 }
@@ -1722,7 +1840,7 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
                 TRY(block_launch<double>(P, 0, kB3Defect, cur, nullptr, b, nullptr, c1.q64, order, st));
                 double* ccur = c1.u64;
                 double* coth = c1.t64;
-                TRY(vcycle_grid_blocks(P, 1, &ccur, &coth, c1.q64, order, true, st));
+                if (!coarse_behind<double>(P, 0)) TRY(vcycle_grid_blocks(P, 1, &ccur, &coth, c1.q64, order, true, st));
                 TRY(read_norms(P, st));
                 rel_prev = cycles == 2 ? 1.0 : rel;
                 rel = std::sqrt(P->hnorm[1]) / r0;
@@ -1873,7 +1991,7 @@ int solve(dmgs_plan P, const double* b, double* x, double bc, int order, dmgs_in
                 else TRY(defect_restrict<double>(P, 0, cur, b, c1.q64, st));
                 double* ccur = c1.u64;
                 double* coth = c1.t64;
-                TRY(vcycle<double>(P, 1, &ccur, &coth, c1.q64, order, true, st));
+                if (!coarse_behind<double>(P, 0)) TRY(vcycle<double>(P, 1, &ccur, &coth, c1.q64, order, true, st));
                 TRY(read_norms(P, st));
                 rel_prev = cycles == 2 ? 1.0 : rel;
                 rel = std::sqrt(P->hnorm[1]) / r0;
@@ -2119,6 +2237,7 @@ int build_hierarchy_grid(dmgs_plan P, hipStream_t st, const double* logD, const 
     hipLaunchKernelGGL(k_g_inverse, dim3(1), dim3(64), (size_t)(2 * m * m * sizeof(double)), st, (const double*)c.D64,
                        (const double*)c.mu64, gdims(P, P->L - 1), P->cinv);
     LAUNCHCHK();
+    TRY(build_tail<double>(P, st));
     if (P->arena) HIPCHK(hipStreamSynchronize(st));
     else HIPCHK(hipEventSynchronize(P->ev_flag));
     if (*P->hflag) {
@@ -2197,6 +2316,7 @@ int build_hierarchy(dmgs_plan P, hipStream_t st, const double* logD = nullptr, c
         }
         LAUNCHCHK();
     }
+    if (!is2d(P) && !wjacobi(P)) TRY(is_ir(P) ? build_tail<float>(P, st) : build_tail<double>(P, st));
     if (P->arena) HIPCHK(hipStreamSynchronize(st));
     else HIPCHK(hipEventSynchronize(P->ev_flag));
     if (*P->hflag) {
@@ -2465,7 +2585,7 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options* o) {
         else b += ((k > 0 ? 3 : 1) + (o->ndim == 2 && k < s.L - 1 ? 1 : 0)) * s.nv[k] * sizeof(double);
     }
     b += (ir ? 2 : 1) * s.nv[0] * sizeof(double);
-    b += kMaxPartials * sizeof(double) + 4 * sizeof(double);
+    b += kMaxPartials * sizeof(double) + 4 * sizeof(double) + 2 * sizeof(int);
     return footprint(o) + b;
 }
 
@@ -2488,6 +2608,8 @@ int kernel_attributes(int device) {
         {(const void*)k_small_vcycle<float, false>, lim32}, {(const void*)k_small_vcycle<float, true>, lim32},
         {(const void*)k_small_vcycle<double, false>, lim64}, {(const void*)k_small_vcycle<double, true>, lim64},
         {(const void*)k_small_grp<float, false>, lim32}, {(const void*)k_small_grp<float, true>, lim32},
+        {(const void*)k_small_cols<float, false>, lim32}, {(const void*)k_small_cols<float, true>, lim32},
+        {(const void*)k_small_cols<double, false>, lim64}, {(const void*)k_small_cols<double, true>, lim64},
         {(const void*)k2_small_vcycle<false>, (int)kSmall2Lds}, {(const void*)k2_small_vcycle<true>, (int)kSmall2Lds}};
     for (const auto& f : fns)
         if (hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, f.second) != hipSuccess) {
@@ -2515,6 +2637,20 @@ int kernel_attributes(int device) {
 // Levels and buffers of a general-grid plan (see plan_init): per level
 // D64, mu64, below the finest u64 and q64, above the coarsest t64 (the
 // defect); the finest scratch, partials, the coarsest inverse, the flag.
+int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst);
+
+// The validation flag and the count of finished workgroups, both 0.
+int clear_flags(dmgs_plan P, hipStream_t zst) {
+    TRY(dalloc(P, &P->dflag, 2));
+    if (P->arena) {
+        hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(64), 0, zst, P->dflag, (int64_t)2, 0);
+        LAUNCHCHK();
+    } else {
+        HIPCHK(hipMemset(P->dflag, 0, 2 * sizeof(int)));
+    }
+    return DMGS_OK;
+}
+
 int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     P->grid = true;
     // the one tuning knob that applies to general grids
@@ -2542,16 +2678,13 @@ int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
         if (k > 0 && st == DMGS_OK) st = dalloc(P, &l.q64, l.nv);
         if (k < P->L - 1 && st == DMGS_OK) st = dalloc(P, &l.t64, l.nv);
     }
-    // first level handled by the single-workgroup kernel, if any
-    for (int k = 1; k < P->L && P->small64 < 0; k++) {
-        int nc[kSmallMaxLevels][3];
-        const int nl = small_counts(P, k, nc);
-        if (small_fits(nc, nl)) P->small64 = k;
-    }
+    choose_small_levels(P);
+    if (P->tail_level >= 0 && st == DMGS_OK)
+        st = dalloc(P, &P->ctail, unknowns(P->lev[P->tail_level]) * unknowns(P->lev[P->tail_level]));
     if (st == DMGS_OK) st = dalloc(P, &P->scratch64, P->lev[0].nv);
     if (st == DMGS_OK) st = dalloc(P, &P->partial, kMaxPartials);
     if (st == DMGS_OK) st = dalloc(P, &P->cinv, kGridCoarseMax * kGridCoarseMax);
-    if (st == DMGS_OK) st = dalloc(P, &P->dflag, 1);
+    if (st == DMGS_OK) st = clear_flags(P, zst);
     if (P->arena) {
         if (st == DMGS_OK) st = dalloc(P, &P->dnorm, 4);
         P->hnorm = P->hnorm_buf;
@@ -2651,8 +2784,10 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     if (ir && st == DMGS_OK) st = dalloc(P, &P->xalt64, P->lev[0].nv);
     if (st == DMGS_OK) st = dalloc(P, &P->partial, kMaxPartials);
     if (st == DMGS_OK) st = dalloc(P, &P->cinv, kCoarseMax * kCoarseMax);
-
-    if (st == DMGS_OK) st = dalloc(P, &P->dflag, 1);
+    if (o->ndim != 2 && st == DMGS_OK) choose_small_levels(P);
+    if (P->tail_level >= 0 && st == DMGS_OK)
+        st = dalloc(P, &P->ctail, unknowns(P->lev[P->tail_level]) * unknowns(P->lev[P->tail_level]));
+    if (st == DMGS_OK) st = clear_flags(P, zst);
     if (P->arena) {
         if (st == DMGS_OK) st = dalloc(P, &P->dnorm, 4);
         P->hnorm = P->hnorm_buf;
@@ -2699,8 +2834,6 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     }
     P->cfg_sweep = 0;
     P->cfg_fuse_min = kn.fuse_min;
-    // first level handled by the single-workgroup kernel (at most 16 cells per axis)
-    P->small32 = P->small64 = -1;
     P->small2 = -1;
     int small2_max = kSmall2MaxN;
     if (const char* e = std::getenv("DMGS_2D_SMALL_MAX")) small2_max = std::min(kSmall2MaxN, std::atoi(e));
@@ -2709,14 +2842,6 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
             P->small2 = k;
             break;
         }
-    for (int k = 1; k < P->L && st == DMGS_OK && o->ndim != 2; k++) {
-        int nc[kSmallMaxLevels][3];
-        const int nl = small_counts(P, k, nc);
-        if (small_fits(nc, nl)) {
-            P->small32 = P->small64 = k;
-            break;
-        }
-    }
     if (st == DMGS_OK) st = kernel_attributes(P->device);
     P->cfg_block_max = kn.block_max;
     // float64 plans: twice the workgroups (each moves twice the bytes of a
@@ -2872,6 +2997,8 @@ int make_twin(dmgs_plan P) {
     T->small32 = P->small32;
     T->small64 = P->small64;
     T->cinv = P->cinv;
+    T->ctail = P->ctail;
+    T->tail_level = P->tail_level;
     const bool ir = is_ir(P);
     int st = DMGS_OK;
     for (int k = 0; k < P->L && st == DMGS_OK; k++) {
@@ -2902,6 +3029,7 @@ int make_twin(dmgs_plan P) {
     if (st == DMGS_OK) st = dalloc(T, &T->scratch64, T->lev[0].nv);
     if (ir && st == DMGS_OK) st = dalloc(T, &T->xalt64, T->lev[0].nv);
     if (st == DMGS_OK) st = dalloc(T, &T->partial, kMaxPartials);
+    if (st == DMGS_OK) st = clear_flags(T, nullptr);
     if (st == DMGS_OK && hipHostMalloc((void**)&T->hnorm, 4 * sizeof(double), hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         set_error("hipHostMalloc failed");
@@ -3543,10 +3671,10 @@ int dmgs_solve_once_noalloc(const dmgs_options* o, const double* D, const double
                             dmgs_info* info, void* stream) {
     TRY(check_options(o));
     if (!D || !mua || !q || !rho) { set_error("NULL argument"); return DMGS_ERR_INVALID; }
-    const size_t need = footprint(o) + kArenaSlack;
+    const size_t need = footprint(o, true) + kArenaSlack;
     if (need > (size_t)DMGS_NOALLOC_SCRATCH_BYTES) {
         set_error("dmgs_solve_once_noalloc: the plan needs %zu bytes (workspace %zu plus alignment), more than the "
-                  "%zu bytes of the static scratch", need, footprint(o), (size_t)DMGS_NOALLOC_SCRATCH_BYTES);
+                  "%zu bytes of the static scratch", need, footprint(o, true), (size_t)DMGS_NOALLOC_SCRATCH_BYTES);
         return DMGS_ERR_INVALID;
     }
     int dev = 0;

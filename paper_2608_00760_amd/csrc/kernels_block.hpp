@@ -213,7 +213,8 @@ struct Block3Shape {
 template <class T, int MODE, bool GEN>
 constexpr size_t block3_lds() { return (size_t)8 * Block3Shape<MODE, GEN>::S * sizeof(T); }
 
-template <class T, int MODE, bool HARM, bool GEN>
+// COHERENT: qc is stored past the caches, for a reader in the same launch.
+template <class T, int MODE, bool HARM, bool GEN, bool COHERENT = false>
 __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bid) {
     using Sh = Block3Shape<MODE, GEN>;
     constexpr int NB = Sh::NB, S = Sh::S, X = Sh::X, Y = Sh::Y;
@@ -389,7 +390,9 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
         const bool mine = act && lx >= Sh::CLO && lx < Sh::CHI && ly >= Sh::CLO && ly < Sh::CHI && lz >= Sh::CLO && lz < Sh::CHI;
         if (mine && inner[0][0] && inner[1][0] && inner[2][0]) {   // a coarse interior vertex
             const T s = a.order ? B3::template weighted<1>(base, idx) : B3::template weighted<0>(base, idx);
-            a.qc[((g[0] >> 1) * (a.n[1] / 2 + 1) + (g[1] >> 1)) * (a.n[2] / 2 + 1) + (g[2] >> 1)] = s * T(1.0 / 64.0);
+            T* const qv = a.qc + ((g[0] >> 1) * (a.n[1] / 2 + 1) + (g[1] >> 1)) * (a.n[2] / 2 + 1) + (g[2] >> 1);
+            if (COHERENT) __hip_atomic_store(qv, s * T(1.0 / 64.0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else *qv = s * T(1.0 / 64.0);
         }
     }
 }

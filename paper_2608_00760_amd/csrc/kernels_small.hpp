@@ -54,7 +54,9 @@ struct SmallArgs {
     SmallLevel<T> lev[kSmallMaxLevels];
     const T* q;                        // right-hand side on the first small level
     T* u;                              // result on the first small level (boundary layer not written)
-    const double* cinv;                // inverse of the coarsest operator (m x m)
+    const double* cinv;                // the last level's solution operator (m x m, row-major): the coarsest
+                                       // operator's inverse, or the matrix of the cycle below it
+    int ctrans;                        // apply its transpose
     int nu_pre, nu_post, order;
     int from_mu;                       // lev[].w holds mua: the inverse diagonal is formed here
 };
@@ -82,7 +84,7 @@ __device__ __forceinline__ int small_at(int off, int x, int y, int z) {
 
 template <class T>
 constexpr size_t small_lds_bytes() {
-    return kSmallWords * sizeof(T) + kSmallCoarseMax * kSmallCoarseMax * sizeof(double);
+    return kSmallWords * sizeof(T) + (kSmallCoarseMax + 1) * kSmallCoarseMax * sizeof(double);
 }
 
 // Whether levels nc[0 .. nlev-1] (cells per axis) fit the kernel.
@@ -105,10 +107,41 @@ __device__ __forceinline__ void small_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <class T, bool HARM>
-__device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
-    extern __shared__ __align__(16) unsigned char small_smem[];
-    T* const base = reinterpret_cast<T*>(small_smem);
+// How a call gets its right-hand side and where its result goes.
+//   kSmallPlain  a.q, a.u
+//   kSmallTail   the same as the last workgroup of the launch that restricts
+//                to a.q: loads the coefficients first, then waits for the
+//                count of finished workgroups at `done` to reach `need`
+//   kSmallCols   workgroup j solves for unit vector j of the first level's
+//                unknowns and writes column j of the cycle's matrix (m x m,
+//                row-major) to `mat`
+enum SmallMode { kSmallPlain = 0, kSmallTail = 1, kSmallCols = 2 };
+
+// One wait per launch, by its last workgroup, for the others of the same
+// launch, which were dispatched before it and wait for nothing: it ends when
+// they do.  The count is back at 0 when the launch ends.
+__device__ __forceinline__ void small_wait(unsigned* done, unsigned need) {
+    if (threadIdx.x == 0) {
+        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+}
+// ... and what the other workgroups do once their stores are issued: the
+// restricted values are stored past the caches (block3_body with COHERENT),
+// so each wave only waits for its own stores to complete.
+__device__ __forceinline__ void small_arrive(unsigned* done) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <class T, bool HARM, int MODE, int NT = kSmallThreads>
+__device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a, unsigned* done = nullptr, unsigned need = 0,
+                                                  double* mat = nullptr) {
+    extern __shared__ __align__(16) unsigned char block_smem[];
+    T* const base = reinterpret_cast<T*>(block_smem);
     const int tid = threadIdx.x, L = a.nlev;
     const int first = a.order ? 1 : 0;       // colour of the first half-sweep
     // this wave's level: 0 for waves 0 .. 7, 1 and 2 for waves 8 and 9
@@ -125,15 +158,17 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
     constexpr int S = kSmallS;
     const int idx = small_off(ml) + bx * kSmallX + by * kSmallY + bz;     // own octant o: base[idx + o S]
     // the coarsest operator's inverse (transposed)
-    double* const sinv = reinterpret_cast<double*>(small_smem + kSmallWords * sizeof(T));
+    double* const sinv = reinterpret_cast<double*>(block_smem + kSmallWords * sizeof(T));
     const int cx = a.lev[L - 1].nc[0] - 1, cy = a.lev[L - 1].nc[1] - 1, cz = a.lev[L - 1].nc[2] - 1;
     const int m = cx * cy * cz;
-    if (L == 1) {   // nothing to smooth: u = A^-1 q straight from memory
+    if (MODE != kSmallCols && L == 1) {   // nothing to smooth: u = A^-1 q straight from memory
+        if (MODE == kSmallTail) small_wait(done, need);
         if (tid < m) {
             const int n1 = cy + 2, n2 = cz + 2;
             auto gid = [&](int c) { return ((1 + c / (cy * cz)) * n1 + 1 + (c / cz) % cy) * n2 + 1 + c % cz; };
             double acc = 0.0;
-            for (int c = 0; c < m; c++) acc += a.cinv[tid * m + c] * (double)a.q[gid(c)];
+            for (int c = 0; c < m; c++) acc += a.cinv[a.ctrans ? c * m + tid : tid * m + c] *
+                       (double)__hip_atomic_load(a.q + gid(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             a.u[gid(tid)] = (T)acc;
         }
         return;
@@ -148,30 +183,30 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
     auto vert = [&](int o) { return v0 + (o >> 2) * n1 * n2 + ((o >> 1) & 1) * n2 + (o & 1); };
     const int ev[3] = {n1 * n2, n2, 1};
     const bool edge[3] = {act && bx == nb0 - 1, act && by == nb1 - 1, act && bz == nb2 - 1};
+    struct Pair {   // two vertices along z, aligned as one
+        T a, b;
+    };
+    auto load = [&](const T* p, bool on, T none, T* v) {
+#pragma unroll
+        for (int o = 0; o < 8; o += 2) {
+            const Pair t = on ? *reinterpret_cast<const Pair*>(p + vert(o)) : Pair{none, none};
+            v[o] = t.a;
+            v[o + 1] = t.b;
+        }
+    };
     {
         // every global load before the first use of one
         T D[8], De[3][4];
-        struct Pair {   // two vertices along z, aligned as one
-            T a, b;
-        };
-        auto load = [&](const T* p, bool on, T none, T* v) {
-#pragma unroll
-            for (int o = 0; o < 8; o += 2) {
-                const Pair t = on ? *reinterpret_cast<const Pair*>(p + vert(o)) : Pair{none, none};
-                v[o] = t.a;
-                v[o + 1] = t.b;
-            }
-        };
         load(lv.D, act, T(1), D);
         load(lv.w, act, T(0), P.w);
-        load(a.q, act && ml == 0, T(0), P.q);
+        if (MODE == kSmallPlain) load(a.q, act && ml == 0, T(0), P.q);
 #pragma unroll
         for (int ax = 0; ax < 3; ax++)
 #pragma unroll
             for (int o = 0; o < 8; o++)
                 if (o & B3::bit(ax)) De[ax][B3::inner(ax, o)] = edge[ax] ? lv.D[vert(o) + ev[ax]] : T(0);
-        for (int i = tid; i < kSmallWords; i += kSmallThreads) base[i] = T(0);
-        for (int i = tid; i < m * m; i += kSmallThreads) sinv[(i % m) * m + i / m] = a.cinv[i];
+        for (int i = tid; i < kSmallWords; i += NT) base[i] = T(0);
+        for (int i = tid; i < m * m; i += NT) sinv[a.ctrans ? i : (i % m) * m + i / m] = a.cinv[i];
         __syncthreads();
 #pragma unroll
         for (int ax = 0; ax < 3; ax++)
@@ -200,6 +235,21 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
 #pragma unroll
         for (int o = 0; o < 8; o++)
             if ((o & B3::bit(ax)) && edge[ax]) base[idx + B3::outer(ax, o)] = T(0);
+
+    if (MODE == kSmallTail) {
+        small_wait(done, need);
+#pragma unroll
+        for (int o = 0; o < 8; o++)
+            P.q[o] = act && ml == 0 ? __hip_atomic_load(a.q + vert(o), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : T(0);
+    } else if (MODE == kSmallCols) {
+        // unknowns of the first level in x, y, z order
+#pragma unroll
+        for (int o = 0; o < 8; o++) {
+            const int x = 2 * bx + (o >> 2), y = 2 * by + ((o >> 1) & 1), z = 2 * bz + (o & 1);
+            const int id = ((x - 1) * (lv.nc[1] - 1) + y - 1) * (lv.nc[2] - 1) + z - 1;
+            P.q[o] = ml == 0 && P.w[o] != T(0) && id == (int)blockIdx.x ? T(1) : T(0);
+        }
+    }
 
     auto half_of = [&](int c) {
         if (c) P.template half<1, false>(base, idx);
@@ -259,12 +309,17 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
         }
         __syncthreads();
     }
-    if (tid < m) {   // coarsest level: u = A^-1 q on the interior unknowns (x, y, z order)
-        auto vid = [&](int c) { return small_at(small_off(L - 1), 1 + c / (cy * cz), 1 + (c / cz) % cy, 1 + c % cz); };
-        double acc = 0.0;
-        for (int c = 0; c < m; c++) acc += sinv[c * m + tid] * (double)base[vid(c)];
+    if (wave == 0) {   // the last level: u = C q on the interior unknowns (x, y, z order), one a lane
+        const int at = small_at(small_off(L - 1), 1 + tid / (cy * cz), 1 + (tid / cz) % cy, 1 + tid % cz);
+        double* const sq = sinv + kSmallCoarseMax * kSmallCoarseMax;
+        if (tid < m) sq[tid] = (double)base[at];
         small_wave_sync();
-        base[vid(tid)] = (T)acc;
+        if (tid < m) {
+            double acc = 0.0;
+#pragma unroll 8
+            for (int c = 0; c < m; c++) acc += sinv[c * m + tid] * sq[c];
+            base[at] = (T)acc;
+        }
     }
     __syncthreads();
     for (int l = L - 2; l >= 0; l--) {  // up
@@ -286,14 +341,32 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a) {
     }
     if (ml == 0 && act) {
 #pragma unroll
-        for (int o = 0; o < 8; o++)
-            if (P.w[o] != T(0)) a.u[vert(o)] = P.u[o];   // boundary entries stay 0
+        for (int o = 0; o < 8; o++) {
+            if (P.w[o] == T(0)) continue;   // boundary entries stay 0
+            if (MODE == kSmallCols) {
+                const int x = 2 * bx + (o >> 2), y = 2 * by + ((o >> 1) & 1), z = 2 * bz + (o & 1);
+                const int id = ((x - 1) * (lv.nc[1] - 1) + y - 1) * (lv.nc[2] - 1) + z - 1;
+                mat[(int64_t)id * gridDim.x + blockIdx.x] = (double)P.u[o];
+            } else {
+                a.u[vert(o)] = P.u[o];
+            }
+        }
     }
 }
 
 template <class T, bool HARM>
 __global__ __launch_bounds__(kSmallThreads) void k_small_vcycle(SmallArgs<T> a) {
-    small_vcycle_body<T, HARM>(a);
+    small_vcycle_body<T, HARM, kSmallPlain>(a);
+}
+
+// The matrix of the cycle from a level of at most kSmallCoarseMax unknowns
+// down (once per coefficient set): the cycle is linear and starts from zero,
+// so that level and everything below it is one product with this matrix (and
+// the transposed cycle's with its transpose).  A level of 4^3 and the 2^3
+// below it took 40 % of the chain of steps for 28 unknowns.
+template <class T, bool HARM>
+__global__ __launch_bounds__(kSmallThreads) void k_small_cols(SmallArgs<T> a, double* mat) {
+    small_vcycle_body<T, HARM, kSmallCols>(a, nullptr, 0, mat);
 }
 
 // Grouped form: one workgroup per member.
@@ -302,7 +375,50 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_grp(const Group<SmallAr
     int bid;
     const int m = group_member(g, &bid);
     if (bid < 0) return;
-    small_vcycle_body<T, HARM>(g->a[m]);
+    small_vcycle_body<T, HARM, kSmallPlain>(g->a[m]);
+}
+
+// The block pass that restricts to the coarse kernel's first level, with that
+// kernel as the launch's last workgroup: its coefficients are loaded while the
+// others work, and the gap between two launches is gone.
+template <class T>
+struct BlockTailArgs {
+    Block3Args<T> b;
+    SmallArgs<T> s;
+    unsigned* done;   // 0 between launches
+    int nb;           // workgroups of the block pass
+};
+
+template <int MODE, bool GEN>
+constexpr int block_tail_threads() {
+    return Block3Shape<MODE, GEN>::NT > kSmallThreads ? Block3Shape<MODE, GEN>::NT : kSmallThreads;
+}
+template <class T, int MODE, bool GEN>
+constexpr size_t block_tail_lds() {
+    return block3_lds<T, MODE, GEN>() > small_lds_bytes<T>() ? block3_lds<T, MODE, GEN>() : small_lds_bytes<T>();
+}
+
+template <class T, int MODE, bool HARM, bool GEN>
+__device__ __forceinline__ void block_tail_body(const BlockTailArgs<T>& a, int bid) {
+    if (bid < a.nb) {
+        block3_body<T, MODE, HARM, GEN, true>(a.b, bid);
+        small_arrive(a.done);
+    } else {
+        small_vcycle_body<T, HARM, kSmallTail, block_tail_threads<MODE, GEN>()>(a.s, a.done, (unsigned)a.nb);
+    }
+}
+
+template <class T, int MODE, bool HARM, bool GEN>
+__global__ __launch_bounds__((block_tail_threads<MODE, GEN>())) void k_block_tail(BlockTailArgs<T> a) {
+    block_tail_body<T, MODE, HARM, GEN>(a, blockIdx.x);
+}
+
+template <class T, int MODE, bool HARM>
+__global__ __launch_bounds__((block_tail_threads<MODE, false>())) void k_block_tail_grp(const Group<BlockTailArgs<T>>* g) {
+    int bid;
+    const int m = group_member(g, &bid);
+    if (bid < 0) return;
+    block_tail_body<T, MODE, HARM, false>(g->a[m], bid);
 }
 
 }  // namespace dmgs

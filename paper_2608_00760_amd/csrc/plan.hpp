@@ -119,8 +119,11 @@ struct dmgs_plan_s {
     int small2 = -1;                  // ... of two-dimensional plans
     double* partial = nullptr;     // first-stage reduction partials
     double* cinv = nullptr;        // inverse of the coarsest operator (kCoarseMax^2 entries)
+    double* ctail = nullptr;       // matrix of the cycle from level tail_level down, if any
+    int tail_level = -1;
     double* hnorm = nullptr;       // pinned host memory the reductions write their norms to (4 slots)
-    int* dflag = nullptr;          // device validation flag
+    int* dflag = nullptr;          // device validation flag; [1]: finished workgroups of a block launch with the
+                                   // coarse kernel behind it (0 between launches)
     int* hflag = nullptr;          // pinned host mirror
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     hipEvent_t ev_norm = nullptr;  // recorded after the last norm reduction
