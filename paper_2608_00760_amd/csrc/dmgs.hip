@@ -2625,6 +2625,15 @@ int kernel_attributes(int device) {
     }
     TRY(sweep2_attributes());
     TRY(block_attributes());
+    const std::pair<const void*, size_t> un[] = {
+        {(const void*)k_un_sweeps_rev_b, kUnBlockLds},
+        {(const void*)k_block3_tape<kB3PreZero, false>, block3_lds<double, kB3PreZero, false>()},
+        {(const void*)k_block3_tape<kB3PreZero, true>, block3_lds<double, kB3PreZero, false>()}};
+    for (const auto& f : un)
+        if (hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.second) != hipSuccess) {
+            (void)hipGetLastError(); set_error("hipFuncSetAttribute failed");
+            return DMGS_ERR_HIP;
+        }
     if (device >= 0 && device < kDevices) done[device] = true;
     return DMGS_OK;
 }
@@ -3224,6 +3233,88 @@ const double* pre_state(dmgs_plan P, UnWork& W, int k) {
     return nu1 > 0 ? W.tape[k][2 * nu1 - 1] : W.tape[k][2 * (nu1 + nu2)];
 }
 
+// Levels of the unrolled adjoint whose V(2,2) phases run in register blocks
+// (up to 64^3, where one round of workgroups holds the level; above, the
+// column tiles read less).
+constexpr int kUnBlockMax = 64;
+bool un_blocks(dmgs_plan P, int k) {
+    return k < P->L - 1 && P->lev[k].N <= kUnBlockMax && P->lev[k].N >= 4 && P->opt.nu_pre == 2 && P->opt.nu_post == 2;
+}
+
+// One recorded block phase of level k: mode kB3PreZero or kB3Sweep (slots 0
+// .. 3 from u_in; kB3PreZero also restricts to qc), kB3Defect (restricts
+// u_in's defect to qc) or kB3Post (slots 4 .. 7 from u_in + I ec).
+int un_block_phase(dmgs_plan P, UnWork& W, int k, int mode, const double* u_in, const double* q, const double* ec,
+                   double* qc, hipStream_t st) {
+    const Level& l = P->lev[k];
+    Block3Args<double> a{};
+    unsigned nb = 1;
+    a.u_in = u_in;
+    a.q = q;
+    a.D = l.D64;
+    a.w = l.w64;
+    a.ec = ec;
+    a.qc = qc;
+    a.tape = W.tape[k][mode == kB3Post ? 4 : 0];
+    a.tape_step = W.tape[k][1] - W.tape[k][0];
+    for (int h = 0; h < 8; h++) UNCHK(W, W.tape[k][h], l.nv, "a tape slot");
+    if (u_in) UNCHK(W, u_in, l.nv, "a phase's input");
+    if (qc) UNCHK(W, qc, P->lev[k + 1].nv, "the coarse right-hand side");
+    auto go = [&](auto Mc, auto Hc) {
+        constexpr int M = decltype(Mc)::value;
+        constexpr bool H = decltype(Hc)::value;
+        for (int x = 0; x < 3; x++) {
+            a.n[x] = l.N;
+            a.s[x] = (H ? 2.0 : 0.5) * l.inv_h2;
+            a.nt[x] = Block3Shape<M, false>::tiles(l.N);
+            nb *= (unsigned)a.nt[x];
+        }
+        if constexpr (M == kB3Defect)
+            hipLaunchKernelGGL((k_block3<double, M, H, false>), dim3(nb), dim3(Block3Shape<M, false>::NT),
+                               (block3_lds<double, M, false>()), st, a);
+        else
+            hipLaunchKernelGGL((k_block3_tape<M, H>), dim3(nb), dim3(Block3Shape<M, false>::NT),
+                               (block3_lds<double, M, false>()), st, a);
+    };
+    auto pick = [&](auto Mc) {
+        if (harmonic(P)) go(Mc, std::true_type());
+        else go(Mc, std::false_type());
+    };
+    if (mode == kB3PreZero) pick(std::integral_constant<int, kB3PreZero>());
+    else if (mode == kB3Sweep) pick(std::integral_constant<int, kB3Sweep>());
+    else if (mode == kB3Defect) pick(std::integral_constant<int, kB3Defect>());
+    else pick(std::integral_constant<int, kB3Post>());
+    LAUNCHCHK();
+    return DMGS_OK;
+}
+
+// Reverse of the phase recorded in slots h0 .. h0 + 3 of level k: ubar into
+// its partner buffer, the accumulators in place (fresh: qbar from 0).
+int un_block_rev(dmgs_plan P, UnWork& W, int k, int h0, bool fresh, hipStream_t st) {
+    const Level& l = P->lev[k];
+    UnBlockArgs a;
+    a.ubar_in = W.ubar[k];
+    a.ubar_out = W.V[k];
+    for (int h = 0; h < 4; h++) {
+        UNCHK(W, W.tape[k][h0 + h], l.nv, "a recorded state");
+        a.state[h] = W.tape[k][h0 + h];
+    }
+    a.D = l.D64;
+    a.w = l.w64;
+    a.qbar = W.qbar[k];
+    a.mubar = W.mbar[k];
+    a.Dbar = W.Dbar[k];
+    a.N = l.N;
+    a.nt = un_block_tiles(l.N);
+    a.fresh = fresh ? 1 : 0;
+    a.s = 0.5 * l.inv_h2;
+    const dim3 grid((unsigned)(a.nt * a.nt * a.nt));
+    hipLaunchKernelGGL(k_un_sweeps_rev_b, grid, dim3(kUnThreads), kUnBlockLds, st, a);
+    LAUNCHCHK();
+    std::swap(W.ubar[k], W.V[k]);
+    return DMGS_OK;
+}
+
 // One V-cycle of the fixed-cycle solver with the per-operator kernels,
 // recording the states the reverse pass needs: each half-sweep writes its
 // result out of place into its tape slot and the next one reads it there.
@@ -3238,11 +3329,33 @@ int vcycle_taped(dmgs_plan P, UnWork& W, int k, double* u, const double* q, cons
     if (k > 0) UNCHK(W, q, l.nv, "the coarse right-hand side");
     if (k == P->L - 1) {
         UNCHK(W, W.tape[k][0], l.nv, "the coarsest tape slot");
-        hipLaunchKernelGGL(k_exact_solve<double>, dim3(1), dim3(64), 0, st, q, u, (const double*)l.D64,
+        if (k == 0) {   // a single-level grid: the boundary values of u are the solve's
+            hipLaunchKernelGGL(k_exact_solve<double>, dim3(1), dim3(64), 0, st, q, u, (const double*)l.D64,
+                               (const double*)l.mu64, l.N, s);
+            LAUNCHCHK();
+            HIPCHK(hipMemcpyAsync(W.tape[k][0], u, bytes, hipMemcpyDeviceToDevice, st));
+            *fin = u;
+            return DMGS_OK;
+        }
+        // straight into the slot, whose boundary is 0
+        hipLaunchKernelGGL(k_exact_solve<double>, dim3(1), dim3(64), 0, st, q, W.tape[k][0], (const double*)l.D64,
                            (const double*)l.mu64, l.N, s);
         LAUNCHCHK();
-        HIPCHK(hipMemcpyAsync(W.tape[k][0], u, bytes, hipMemcpyDeviceToDevice, st));
-        *fin = u;
+        *fin = W.tape[k][0];
+        return DMGS_OK;
+    }
+    if (un_blocks(P, k)) {
+        double* qc = W.qc[k + 1];
+        if (k > 0) {
+            TRY(un_block_phase(P, W, k, kB3PreZero, nullptr, q, nullptr, qc, st));
+        } else {
+            TRY(un_block_phase(P, W, k, kB3Sweep, u, q, nullptr, nullptr, st));
+            TRY(un_block_phase(P, W, k, kB3Defect, W.tape[k][3], q, nullptr, qc, st));
+        }
+        const double* ec = nullptr;
+        TRY(vcycle_taped(P, W, k + 1, W.uc[k + 1], qc, &ec, st));
+        TRY(un_block_phase(P, W, k, kB3Post, W.tape[k][3], q, ec, nullptr, st));
+        *fin = W.tape[k][7];
         return DMGS_OK;
     }
     int chunk = 1, cover = 0;
@@ -3297,7 +3410,7 @@ int vcycle_taped(dmgs_plan P, UnWork& W, int k, double* u, const double* q, cons
     // qc = R (q - A u) in one streaming pass, the defect at every fine vertex
     // (coarse boundary entries are not written; no step reads them)
     TRY(defect_restrict<double>(P, k, src, q, W.qc[k + 1], st));
-    TRY(fill<double>(W.uc[k + 1], c.nv, 0.0, st));
+    if (!un_blocks(P, k + 1) && k + 1 < P->L - 1) TRY(fill<double>(W.uc[k + 1], c.nv, 0.0, st));
     const double* ec = nullptr;
     TRY(vcycle_taped(P, W, k + 1, W.uc[k + 1], W.qc[k + 1], &ec, st));
     // the post-smoothing input: the pre-smoothed state plus the correction,
@@ -3387,7 +3500,9 @@ int vcycle_rev(dmgs_plan P, UnWork& W, int k, hipStream_t st) {
         std::swap(W.ubar[k], W.V[k]);
         return DMGS_OK;
     };
-    for (int h = 2 * nu2 - 1; h >= 1; h -= 2) TRY(sweep_rev(W.tape[k][2 * nu1 + h], W.tape[k][2 * nu1 + h - 1]));
+    const bool blocks = un_blocks(P, k) && !harmonic(P);   // the reverse blocks take the arithmetic face mean
+    if (blocks) TRY(un_block_rev(P, W, k, 4, k > 0, st));
+    for (int h = 2 * nu2 - 1; h >= 1 && !blocks; h -= 2) TRY(sweep_rev(W.tape[k][2 * nu1 + h], W.tape[k][2 * nu1 + h - 1]));
     // prolongation u += I ec: ecbar = I^T ubar = 8 R ubar
     const Level& c = P->lev[k + 1];
     UNCHK(W, W.ubar[k + 1], c.nv, "the coarse ubar");
@@ -3397,7 +3512,7 @@ int vcycle_rev(dmgs_plan P, UnWork& W, int k, hipStream_t st) {
     hipLaunchKernelGGL(k_un_restrict8, dim3(grid_for(c.nv)), dim3(kBlock), 0, st, (const double*)W.ubar[k],
                        W.ubar[k + 1], l.N);
     LAUNCHCHK();
-    TRY(fill<double>(W.qbar[k + 1], c.nv, 0.0, st));
+    if (!(un_blocks(P, k + 1) && !harmonic(P))) TRY(fill<double>(W.qbar[k + 1], c.nv, 0.0, st));   // else set by its first phase
     TRY(vcycle_rev(P, W, k + 1, st));
     // restriction qc = R r: rbar = R^T qcbar = I qcbar / 8; then the defect
     hipLaunchKernelGGL(k_un_prolong_to, dim3(grid_for(l.nv)), dim3(kBlock), 0, st, (const double*)W.qbar[k + 1],
@@ -3405,7 +3520,8 @@ int vcycle_rev(dmgs_plan P, UnWork& W, int k, hipStream_t st) {
     LAUNCHCHK();
     defect_rev(W.ubar[k], (const double*)W.r[k], 0.125, pre_state(P, W, k));
     LAUNCHCHK();
-    for (int h = 2 * nu1 - 1; h >= 1; h -= 2) TRY(sweep_rev(W.tape[k][h], W.tape[k][h - 1]));
+    if (blocks) TRY(un_block_rev(P, W, k, 0, false, st));
+    for (int h = 2 * nu1 - 1; h >= 1 && !blocks; h -= 2) TRY(sweep_rev(W.tape[k][h], W.tape[k][h - 1]));
     return DMGS_OK;
 }
 }  // namespace
@@ -3456,11 +3572,17 @@ int dmgs_vjp_unrolled(dmgs_plan P, const double* q, const double* rhobar, double
             for (int c = 0; c < nsets; c++) {
                 double* b = nullptr;
                 TRY(W.alloc(&b, per));
+                // block phases and the coarsest solve write interior entries
+                // only: the slots' boundary is 0, on the finest level bc
+                TRY(fill<double>(b, per, 0.0, st));
                 int64_t off = 0;
                 for (int k = 0; k < L; k++) {
                     const int ns = k == L - 1 ? 1 : nstate;
-                    for (int h = 0; h < ns; h++, off += up(P->lev[k].nv))
+                    for (int h = 0; h < ns; h++, off += up(P->lev[k].nv)) {
                         W.sets[((size_t)c * kMaxLevels + k) * 33 + h] = b + off;
+                        if (k == 0 && un_blocks(P, 0) && o.bc_value != 0.0)
+                            TRY(set_boundary<double>(b + off, P->lev[0].N, o.bc_value, st));
+                    }
                 }
             }
             W.use_cycle(0);

@@ -191,6 +191,8 @@ struct Block3Args {
     int order;         // colour of the first half-sweep
     const double *ed, *ew;   // kB3PostEpi: data, inverse variances
     double* rhobar;          // ... and dH/drho
+    T* tape;                 // TAPE: the iterate after half-sweep j at tape + j tape_step (interior written);
+    int64_t tape_step;       // u_out is not written
 };
 
 template <int MODE, bool GEN>
@@ -214,7 +216,8 @@ template <class T, int MODE, bool GEN>
 constexpr size_t block3_lds() { return (size_t)8 * Block3Shape<MODE, GEN>::S * sizeof(T); }
 
 // COHERENT: qc is stored past the caches, for a reader in the same launch.
-template <class T, int MODE, bool HARM, bool GEN, bool COHERENT = false>
+// TAPE: every half-sweep's state is kept (the unrolled adjoint's record).
+template <class T, int MODE, bool HARM, bool GEN, bool COHERENT = false, bool TAPE = false>
 __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bid) {
     using Sh = Block3Shape<MODE, GEN>;
     constexpr int NB = Sh::NB, S = Sh::S, X = Sh::X, Y = Sh::Y;
@@ -335,20 +338,24 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
         if (tid == 0) a.partial[bid] = sum;
     }
     if (MODE != kB3Defect) {
+        auto store = [&](T* out) {
+            if (!act) return;
+            const int v0 = (g[0] * n1 + g[1]) * n2 + g[2];
+#pragma unroll
+            for (int o = 0; o < 8; o++)
+                if (of(tile, o) && of(inner, o)) out[v0 + ((o >> 2) * n1 + ((o >> 1) & 1)) * n2 + (o & 1)] = P.u[o];
+        };
+        if (TAPE && MODE == kB3PreZero) store(a.tape);
         // the first half-sweep from zero was u = w q
         for (int j = MODE == kB3PreZero ? 1 : 0; j < 4; j++) {
             if (act) {
                 if ((j & 1) ? !a.order : a.order) P.template half<1, true>(base, idx);
                 else P.template half<0, true>(base, idx);
             }
+            if (TAPE) store(a.tape + j * a.tape_step);
             __syncthreads();
         }
-        if (act) {
-            const int v0 = (g[0] * n1 + g[1]) * n2 + g[2];
-#pragma unroll
-            for (int o = 0; o < 8; o++)
-                if (of(tile, o) && of(inner, o)) a.u_out[v0 + ((o >> 2) * n1 + ((o >> 1) & 1)) * n2 + (o & 1)] = P.u[o];
-        }
+        if (!TAPE) store(a.u_out);
     }
     if constexpr (MODE == kB3PostEpi) {
         double acc = 0.0, cnt = 0.0;
@@ -400,6 +407,11 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
 template <class T, int MODE, bool HARM, bool GEN>
 __global__ __launch_bounds__((Block3Shape<MODE, GEN>::NT)) void k_block3(Block3Args<T> a) {
     block3_body<T, MODE, HARM, GEN>(a, blockIdx.x);
+}
+
+template <int MODE, bool HARM>
+__global__ __launch_bounds__((Block3Shape<MODE, false>::NT)) void k_block3_tape(Block3Args<double> a) {
+    block3_body<double, MODE, HARM, false, false, true>(a, blockIdx.x);
 }
 
 template <class T, int MODE, bool HARM>

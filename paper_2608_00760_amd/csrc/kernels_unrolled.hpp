@@ -19,15 +19,180 @@
 // kernels_deriv.hpp and take a whole red-black sweep per pass: the recorded
 // sweep (k_un_gs_sweep_t), its reverse (k_un_sweep_rev_t), and the defect's
 // reverse (k_un_defect_t), with each plane's neighbours over the tile plus a
-// ring in LDS.  Smaller levels march one thread per plane vertex (UnCol),
-// one half-sweep per pass.  The rest take one vertex per thread.
+// ring in LDS.  Levels of at most 64 cells run whole V(2,2) phases in
+// register blocks: the recorded ones (k_block3_tape) and their reverse
+// (k_un_sweeps_rev_b).  Between, and with other smoothing counts, levels
+// march one thread per plane vertex (UnCol), one half-sweep per pass.  The
+// rest take one vertex per thread.
 // Cotangents are 0 on boundary vertices except Dbar, which boundary faces
 // reach.
 #pragma once
 #include "kernels_basic.hpp"
+#include "kernels_block.hpp"
 #include "kernels_deriv.hpp"
 
 namespace dmgs {
+
+// Reverse of a V(2,2) phase's two sweeps (four half-sweeps, the last first)
+// in blocks of 2 x 2 x 2 vertices, arithmetic face mean: boxes of 16^3 around
+// tiles of 8^3, ubar on the tile and its coefficient terms from the box's
+// ubar, four rings away (what is formed nearer to the box's edge is wrong by
+// one ring more per half-sweep and read by nothing that is kept).  With c_ij =
+// (D_i + D_j) / (2 h^2) a vertex of the other colour gains
+//   sum_j c_ij V_j = (D_i sum_j V_j + sum_j D_j V_j) / (2 h^2),
+// so V and D V are published and no face coefficient is held; a face (i, j)
+// carries V (u_i - u_j) of its end of the half's colour to both ends' Dbar,
+// and dc/dD = 1 / (2 h^2) comes once, at the end.  (Holding the 36 face
+// coefficients as the smoothing blocks do leaves this kernel 94 registers
+// short: 30 us for one workgroup.)  Bound by latency and by one CU's float64
+// arithmetic: 14 us for one workgroup, 17 us for 64 (32^3), 35 us at 64^3, where
+// eight half-sweep launches took 56 us (8^3: 25 us).
+struct UnBlockArgs {
+    const double* ubar_in;
+    double* ubar_out;                 // interior of the level (boundary entries are 0 in both)
+    const double* state[4];           // after half-sweep 0 .. 3 of the phase
+    const double *D, *w;
+    double *qbar, *mubar, *Dbar;      // accumulated
+    int N, nt;                        // cells per axis, tiles per axis
+    int fresh;                        // qbar starts at 0 here (its contents are not read)
+    double s;                         // 1 / (2 h^2)
+};
+
+constexpr int kUnB = 8, kUnS = kUnB * kUnB * kUnB, kUnThreads = kUnS;
+constexpr size_t kUnBlockLds = (size_t)3 * 8 * kUnS * sizeof(double);
+__host__ __device__ constexpr int un_block_tiles(int N) { return (N + 7) / 8; }
+
+__global__ __launch_bounds__(kUnThreads) void k_un_sweeps_rev_b(UnBlockArgs a) {
+    using B3 = Block3<double, kUnS, kUnB * kUnB, kUnB>;   // octants, neighbours, strides
+    struct VW {
+        double v, w;   // V, D V
+    };
+    extern __shared__ __align__(16) unsigned char block_smem[];
+    VW* const sV = reinterpret_cast<VW*>(block_smem);
+    double* const sU = reinterpret_cast<double*>(sV + 8 * kUnS);
+    const int tid = threadIdx.x;
+    const int lz = tid & 7, ly = (tid >> 3) & 7, lx = tid >> 6, idx = tid;
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    const int t3[3] = {b / (a.nt * a.nt), (b / a.nt) % a.nt, b % a.nt};
+    const int l3[3] = {lx, ly, lz};
+    const int N = a.N, n = N + 1;
+    int g[3];
+    bool in[3][2], inner[3][2], tile[3][2];   // per axis and bit
+#pragma unroll
+    for (int ax = 0; ax < 3; ax++) {
+        g[ax] = 8 * t3[ax] - 4 + 2 * l3[ax];
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int c = g[ax] + k;
+            in[ax][k] = c >= 0 && c <= N;
+            inner[ax][k] = c > 0 && c < N;
+            // the last tile of an axis takes the grid's last vertices too
+            tile[ax][k] = in[ax][k] && ((l3[ax] >= 2 && l3[ax] < 6) || (c == N && t3[ax] == a.nt - 1));
+        }
+    }
+    auto of = [](const bool (&f)[3][2], int o) { return f[0][o >> 2] && f[1][(o >> 1) & 1] && f[2][o & 1]; };
+    int row[4];   // rows of the block, clamped to the grid; at z = N the pair read is (N - 1, N)
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        row[k] = (min(max(g[0] + (k >> 1), 0), N) * n + min(max(g[1] + (k & 1), 0), N)) * n + min(max(g[2], 0), N - 1);
+    struct Pair {
+        double a, b;
+    };
+    auto load = [&](const double* p, double* v) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const Pair r = *reinterpret_cast<const Pair*>(p + row[k]);
+            v[2 * k] = g[2] == N ? r.b : r.a;
+            v[2 * k + 1] = r.b;
+        }
+    };
+    double D[8], w[8], ub[8], u[8], next[8], acc[8] = {}, vs[8] = {}, ms[8] = {};
+    load(a.D, D);
+    load(a.w, w);
+    load(a.ubar_in, ub);
+    load(a.state[3], u);
+#pragma unroll
+    for (int o = 0; o < 8; o++) {
+        w[o] = of(inner, o) ? w[o] : 0.0;     // no cotangent on the boundary and outside
+        ub[o] = of(inner, o) ? ub[o] : 0.0;
+        u[o] = of(in, o) ? u[o] : 0.0;
+    }
+    // a wave without tile vertices (one plane of blocks) needs no face terms
+    const bool faces = __builtin_amdgcn_ballot_w64(tile[0][0] || tile[0][1]) != 0;
+    auto half = [&](auto Cc) {
+        constexpr int C = decltype(Cc)::value;
+        double V[8];
+        __syncthreads();   // the last half's reads of the LDS are done
+#pragma unroll
+        for (int o = 0; o < 8; o++) {
+            sU[idx + o * kUnS] = u[o];
+            if (B3::colour(o) != C) continue;
+            V[o] = ub[o] * w[o];
+            vs[o] += V[o];
+            ms[o] -= V[o] * u[o];
+            ub[o] = 0.0;
+            sV[idx + o * kUnS] = VW{V[o], D[o] * V[o]};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < 8; o++) {
+            double un[3] = {};
+            if (faces) {
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) un[ax] = sU[idx + B3::outer(ax, o)];
+            }
+            if (B3::colour(o) == C) {
+                if (!faces) continue;
+                double d = 0.0;
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) d += (u[o] - un[ax]) + (u[o] - u[o ^ B3::bit(ax)]);
+                acc[o] += V[o] * d;
+            } else {
+                VW vn[3];
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) vn[ax] = sV[idx + B3::outer(ax, o)];
+                double sv = 0.0, sw = 0.0;
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) {
+                    const int p = o ^ B3::bit(ax);
+                    sv += vn[ax].v + V[p];
+                    sw += vn[ax].w + D[p] * V[p];
+                    if (faces) acc[o] += vn[ax].v * (un[ax] - u[o]) + V[p] * (u[p] - u[o]);
+                }
+                if (of(inner, o)) ub[o] += a.s * (D[o] * sv + sw);
+            }
+            // two octants at a time: left alone the compiler moves these sums
+            // past the next half-sweep and keeps 60 of its reads in registers
+            asm volatile("" : "+v"(acc[o]), "+v"(ub[o]));
+            if (o & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto step = [&](auto Cc, int h) {
+        if (h > 0) load(a.state[h - 1], next);
+        half(Cc);
+        if (h > 0) {
+#pragma unroll
+            for (int o = 0; o < 8; o++) u[o] = of(in, o) ? next[o] : 0.0;
+        }
+    };
+#pragma unroll 1
+    for (int h = 3; h > 0; h -= 2) {
+        step(std::integral_constant<int, 1>(), h);
+        step(std::integral_constant<int, 0>(), h - 1);
+    }
+    const int v0 = (g[0] * n + g[1]) * n + g[2];
+#pragma unroll
+    for (int o = 0; o < 8; o++) {
+        if (!of(tile, o)) continue;
+        const int v = v0 + ((o >> 2) * n + ((o >> 1) & 1)) * n + (o & 1);
+        a.Dbar[v] -= acc[o] * a.s;
+        if (of(inner, o)) {
+            a.ubar_out[v] = ub[o];
+            a.qbar[v] = a.fresh ? vs[o] : a.qbar[v] + vs[o];
+            a.mubar[v] += ms[o];
+        }
+    }
+}
 
 // d c_f / d D_a for the face coefficient c_f = face(D_a, D_b) / h^2
 __device__ __forceinline__ double dface_da(double Da, double Db, const Stencil<double>& s) {
