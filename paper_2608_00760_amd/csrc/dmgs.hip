@@ -780,7 +780,7 @@ int smooth_pass2(dmgs_plan P, int k, const T* u_in, T* u_out, const T* q, int or
         return DMGS_ERR_INVALID;
     }
     // algorithmic bytes: read u (unless zero), q, D, w, (ec), write u, (r) -- once for both sweeps
-    double words = (zero ? 4.0 : 5.0) + (ec ? 0.125 : 0.0) + (r ? 1.0 : 0.0);
+    double words = (zero ? 4.0 : 5.0) + (ec ? 0.125 : 0.0) + (r ? 0.5 : 0.0);
     int slot;
     TRY(tbeg(P, k, st, &slot, DMGS_K_SMOOTH));
     if constexpr (sizeof(T) == 4) {
@@ -808,28 +808,36 @@ int smooth_pass2(dmgs_plan P, int k, const T* u_in, T* u_out, const T* q, int or
 
 // Chunks of coarse planes sized for about cfg_dr_wgs workgroups (each
 // chunk re-reads the fine planes at its ends), at least 4.
-template <class T, int TYC, int TZC, bool HARM, bool FROM_R>
-int launch_restrict(dmgs_plan P, const RestrictArgs<T>& a0, int Nc, hipStream_t st) {
-    RestrictArgs<T> a = a0;
-    constexpr int NT = RestrictShape<TYC, TZC>::NT;
+template <class T>
+unsigned restrict_grid(dmgs_plan P, RestrictArgs<T>& a, int TYC, int TZC, int group = 0) {
+    const int Nc = a.N / 2;
     a.tiles_y = (Nc - 1 + TYC - 1) / TYC;
     a.tiles_z = (Nc - 1 + TZC - 1) / TZC;
     const int tiles = a.tiles_y * a.tiles_z;
     const int nch = std::max(1, (P->cfg_dr_wgs + tiles - 1) / tiles);
     a.chunk = std::max(4, (Nc - 1 + nch - 1) / nch);
+    // a chunk of c coarse planes marches 2 c + 1 fine ones: whole groups of
+    // `group` planes, nearest to the size wanted; at most 63 planes, so that
+    // the last round of workgroups is a small part (512^3: 84 us with 2304
+    // workgroups, 114 with 768; 256^3: 18 us with 576, 21 with 2752)
+    if (group) a.chunk = std::max(1, (std::min(a.chunk, 32) + 1 + group / 4) / (group / 2)) * (group / 2) - 1;
     if (a.chunk > Nc - 1) a.chunk = Nc - 1;
     a.nchunks = (Nc - 1 + a.chunk - 1) / a.chunk;
-    int nb = a.tiles_y * a.tiles_z * a.nchunks;
-    const void* grp = nullptr;
-    if constexpr (sizeof(T) == 4) grp = (const void*)k_defect_restrict_grp<T, TYC, TZC, HARM, FROM_R>;
-    return launch_rec(P, (const void*)k_defect_restrict_col<T, TYC, TZC, HARM, FROM_R>, grp, (unsigned)nb, NT, 0, a, st);
+    return (unsigned)(tiles * a.nchunks);
 }
 
-// qc = R (q - A u); from_r: u holds the defect itself after pre-smoothing
-// whose first colour was `order` (the other colour's defect is 0), qc = R u.
+template <class T, int TYC, int TZC, bool HARM>
+int launch_restrict(dmgs_plan P, const RestrictArgs<T>& a0, hipStream_t st) {
+    RestrictArgs<T> a = a0;
+    const unsigned nb = restrict_grid(P, a, TYC, TZC);
+    const void* grp = nullptr;
+    if constexpr (sizeof(T) == 4) grp = (const void*)k_defect_restrict_grp<T, TYC, TZC, HARM>;
+    return launch_rec(P, (const void*)k_defect_restrict_col<T, TYC, TZC, HARM>, grp, nb, RestrictShape<TYC, TZC>::NT, 0, a, st);
+}
+
+// qc = R (q - A u).
 template <class T>
-int defect_restrict(dmgs_plan P, int k, const T* u, const T* q, T* qc, hipStream_t st, bool from_r = false,
-                    int order = 0) {
+int defect_restrict(dmgs_plan P, int k, const T* u, const T* q, T* qc, hipStream_t st) {
     const Level& l = P->lev[k];
     const Level& c = P->lev[k + 1];
     RestrictArgs<T> a;
@@ -841,16 +849,42 @@ int defect_restrict(dmgs_plan P, int k, const T* u, const T* q, T* qc, hipStream
     a.py = Typed<T>::py(l);
     a.px = Typed<T>::px(l);
     a.N = l.N;
-    a.rzero = order ? 0 : 1;
     a.st = l.stencil<T>(harmonic(P));
     constexpr int TYC = 8, TZC = sizeof(T) == 4 ? 32 : 16;
     int slot;
     TRY(tbeg(P, k, st, &slot, DMGS_K_DEFECT_RESTRICT));
-    if (from_r) TRY((launch_restrict<T, TYC, TZC, false, true>(P, a, c.N, st)));
-    else if (harmonic(P)) TRY((launch_restrict<T, TYC, TZC, true, false>(P, a, c.N, st)));
-    else TRY((launch_restrict<T, TYC, TZC, false, false>(P, a, c.N, st)));
-    TRY(tend(P, slot, DMGS_K_DEFECT_RESTRICT, ((from_r ? 1.0 : 4.0) * l.nv + c.nv) * sizeof(T), st));
+    if (harmonic(P)) TRY((launch_restrict<T, TYC, TZC, true>(P, a, st)));
+    else TRY((launch_restrict<T, TYC, TZC, false>(P, a, st)));
+    TRY(tend(P, slot, DMGS_K_DEFECT_RESTRICT, (4.0 * l.nv + c.nv) * sizeof(T), st));
     return DMGS_OK;
+}
+
+// qc = R r from the defect a pre-smoothing pass whose first colour was
+// `order` left in the level's r32 (the other colour's is 0).
+template <class T>
+int restrict_half(dmgs_plan P, int k, T* qc, int order, hipStream_t st) {
+    if constexpr (sizeof(T) == 4) {
+        const Level& l = P->lev[k];
+        RestrictArgs<T> a;
+        a.u = l.r32;
+        a.qc = qc;
+        a.py = l.py;
+        a.px = l.px;
+        a.N = l.N;
+        a.order = order;
+        constexpr int TYC = 4, TZC = 64;
+        using Sh = RestrictHalfShape<TYC, TZC>;
+        const unsigned nb = restrict_grid(P, a, TYC, TZC, Sh::NF);
+        int slot;
+        TRY(tbeg(P, k, st, &slot, DMGS_K_DEFECT_RESTRICT));
+        TRY(launch_rec(P, (const void*)k_restrict_half<T, TYC, TZC>, (const void*)k_restrict_half_grp<T, TYC, TZC>, nb,
+                       Sh::NT, 0, a, st));
+        TRY(tend(P, slot, DMGS_K_DEFECT_RESTRICT, (0.5 * l.nv + P->lev[k + 1].nv) * sizeof(T), st));
+        return DMGS_OK;
+    } else {
+        set_error("internal: float64 passes leave no defect");
+        return DMGS_ERR_INVALID;
+    }
 }
 
 // Smoothing phase of `nsweeps` red-black sweeps on level k starting from
@@ -1158,7 +1192,7 @@ int pre_pass(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int orde
         bool rdone;
         T* r = Typed<T>::r(l);
         TRY(smooth_phase<T>(P, k, cur, other, q, nu_pre_of(P, order), order, zero, (const T*)nullptr, st, r, &rdone));
-        return rdone ? defect_restrict<T>(P, k, r, q, qc, st, true, order) : defect_restrict<T>(P, k, *cur, q, qc, st);
+        return rdone ? restrict_half<T>(P, k, qc, order, st) : defect_restrict<T>(P, k, *cur, q, qc, st);
     }
     TRY(need_dense<T>(P, k, "simple pre-smoothing"));
     if (zero) TRY(fill<T>(*cur, l.nv, T(0), st));
@@ -1259,8 +1293,7 @@ int vcycle(dmgs_plan P, int k, T** cur, T** other, const T* q, int order, bool z
     T* qc = Typed<T>::q(c);
     if (smoothed && block_level<T>(P, k)) {
         // the block pass has restricted the defect too
-    } else if (smoothed) TRY(rdone ? defect_restrict<T>(P, k, Typed<T>::r(P->lev[k]), q, qc, st, true, order)
-                            : defect_restrict<T>(P, k, *cur, q, qc, st));
+    } else if (smoothed) TRY(rdone ? restrict_half<T>(P, k, qc, order, st) : defect_restrict<T>(P, k, *cur, q, qc, st));
     else TRY(pre_pass<T>(P, k, cur, other, q, qc, order, zero, st));
     T* ccur = Typed<T>::u(c);
     T* coth = Typed<T>::t(c);

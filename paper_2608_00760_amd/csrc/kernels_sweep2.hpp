@@ -43,14 +43,17 @@
 // With DEFECT the pass also writes the defect r = q - A u of its result on
 // the tile (the restriction of the next coarser right-hand side then reads
 // r alone).  The loaded ring grows to 5 so that the final values are known
-// on the tile plus a ring of 1, the stages run one step earlier and one
+// on the tile plus a ring of 1 (6 in z, whole pairs), the stages run one step earlier and one
 // step longer, the last stage publishes its values to the slot too, and at
 // step s the defect of plane s - 4 is formed from the slots of planes s - 4
 // and s - 5 and the registers of plane s - 3.  After a red-black sweep the
 // residual of the colour updated last is zero (its update solved its own
 // equation with its neighbours' final values), so only the first colour's
-// residual is computed and stored; the reader takes the second colour's as
-// 0.  Waves with no tile vertex skip the defect.
+// residual is computed and stored, one value per pair (a row's pairs all hold
+// it in the same element); k_restrict_half takes the second colour's as 0.
+// Waves with no tile vertex skip the defect.  Half a word a vertex instead of
+// one, and pairs of the iterate stored whole: 848 -> 776 us at 512^3, 75.6 ->
+// 71.6 us at 192^3.
 //
 // With NORM (plain passes) the pass also sums the squared residual of its
 // input over the tile's first-colour vertices: stage 0 forms q + sum_j c_ij
@@ -65,8 +68,9 @@ namespace dmgs {
 
 template <int TY, int TZ, int RING = 4>
 struct Sweep2Shape {
-    static constexpr int R = RING;                           // ring of loaded vertices
-    static constexpr int NP = TZ / 2 + R, RY = TY + 2 * R;   // pairs per row, rows
+    static constexpr int R = RING;                            // ring of loaded vertices
+    static constexpr int RZ = (RING + 1) / 2 * 2;             // ... in z whole pairs: element 0 is at even z
+    static constexpr int NP = TZ / 2 + RZ, RY = TY + 2 * R;   // pairs per row, rows
     static constexpr int RA = RY * NP;                       // pairs per plane (per element)
     static constexpr int ROWS_HALF = RY / 2;
     static constexpr int HALF = (ROWS_HALF * NP + 63) / 64 * 64;
@@ -125,7 +129,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
     const int b = xcd_tile(bid, nb);
     const int bz = b % a.tiles_z, by = (b / a.tiles_z) % a.tiles_y, bx = b / (a.tiles_z * a.tiles_y);
     const int y0 = by * TY, z0 = bz * TZ;
-    const int y = y0 - R + ly, zl = z0 - R + 2 * pz;
+    const int y = y0 - R + ly, zl = z0 - Sh::RZ + 2 * pz;
     const int xa = 1 + bx * a.chunk, xb = min(N, xa + a.chunk);   // output planes [xa, xb)
     const int pe = ly * NP + pz;                                   // this pair's index in a slot
     // in-plane offset of element 0 (element 1 is the next word); rows outside
@@ -144,9 +148,13 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
         m0[j] = in_ring(zl, R - 1 - j);
         m1[j] = in_ring(zl + 1, R - 1 - j);
     }
-    const int soff0 = (own && in_ring(zl, 0)) ? off : kOob;   // tile vertices are stored
-    const int soff1 = (own && in_ring(zl + 1, 0)) ? off + (int)sizeof(T) : kOob;
-    const auto rR = field_rsrc(a.r, DEFECT ? field_bytes : 0);
+    // tile vertices are stored, a pair at a time; of the pair (0, 1) element 0
+    // is a boundary vertex and gets its 0 again
+    const bool in0 = own && in_ring(zl, 0), in1 = own && in_ring(zl + 1, 0);
+    const int soff = in1 ? off : kOob;
+    const int pr = half_pitch(a.py), rplane_bytes = pr * n * (int)sizeof(T);
+    const int roff = in1 ? (y * pr + (zl >> 1)) * (int)sizeof(T) : kOob;
+    const auto rR = field_rsrc(a.r, DEFECT ? n * rplane_bytes : 0);
     const auto rU = field_rsrc(a.u_in, field_bytes), rD = field_rsrc(a.D, field_bytes);
     const auto rQ = field_rsrc(a.q, field_bytes), rW = field_rsrc(a.w, field_bytes);
     const auto rO = field_rsrc(a.u_out, field_bytes);
@@ -299,7 +307,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
         if constexpr (NORM && J == 0) {
             const T num = gs_num(Oc, S, Pb, P, Pa);
             const T wi = O ? P.w1 : P.w0;
-            const bool on = step_in && (O ? soff1 : soff0) != kOob;
+            const bool on = step_in && (O ? in1 : in0);
             const T r = num - (O ? P.u1 : P.u0) / (on ? wi : T(1));
             nacc += on ? (double)r * (double)r : 0.0;
             v = num * wi;
@@ -320,7 +328,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
     // colour of the first half-sweep: x-neighbour below from the slot of
     // plane s - 5, above from the registers of plane s - 3 (final after this
     // step's last stage)
-    const bool dwave = __builtin_amdgcn_ballot_w64(soff0 != kOob || soff1 != kOob) != 0;
+    const bool dwave = __builtin_amdgcn_ballot_w64(in0 || in1) != 0;
     auto defect = [&](auto Oc, auto Kc, int s, const SweepPlane<T>& Pm4, const SweepPlane<T>& Pm3) {
         if (!dwave) return;
         constexpr int O = decltype(Oc)::value, K = decltype(Kc)::value;
@@ -334,7 +342,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
         // rounded in float32 anyway)
         const T r = num - (O ? Pm4.u1 * __builtin_amdgcn_rcpf(Pm4.w1) : Pm4.u0 * __builtin_amdgcn_rcpf(Pm4.w0));
         const int po = s - 4;
-        if (po >= xa && po < xb) buf_store<T>(r, rR, (O ? soff1 : soff0) + po * plane_bytes);
+        if (po >= xa && po < xb) buf_store<T>(O || in0 ? r : T(0), rR, roff + po * rplane_bytes);
     };
     auto stages = [&](auto Oc, auto Kc, SweepPlane<T>& Pm4, SweepPlane<T>& Pm3, SweepPlane<T>& Pm2,
                       SweepPlane<T>& Pm1, SweepPlane<T>& P0, SweepPlane<T>& Pp1) {
@@ -346,7 +354,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
 
     // with DEFECT, final values are needed on planes xa - 1 .. xb
     const int s0 = xa - 3 - (DEFECT ? 1 : 0), s_end = xb + 2 + (DEFECT ? 1 : 0);
-    const int par0 = __builtin_amdgcn_readfirstlane((s0 + hp + a.order) & 1);   // element updated at step s0
+    const int par0 = __builtin_amdgcn_readfirstlane((s0 + hp + R + a.order) & 1);   // element updated at step s0
     auto step = [&](auto Kc, int s, SweepPlane<T>& Pm4, SweepPlane<T>& Pm3, SweepPlane<T>& Pm2, SweepPlane<T>& Pm1,
                     SweepPlane<T>& P0, SweepPlane<T>& Pp1, SweepPlane<T>& Pp3) {
         constexpr int K = decltype(Kc)::value;
@@ -372,8 +380,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
         }
         const int po = s - 3;   // final
         if (po >= xa && po < xb) {
-            buf_store<T>(Pm3.u0, rO, soff0 + po * plane_bytes);
-            buf_store<T>(Pm3.u1, rO, soff1 + po * plane_bytes);
+            buf_store2(Pm3.u0, Pm3.u1, rO, soff + po * plane_bytes);
         }
     };
 

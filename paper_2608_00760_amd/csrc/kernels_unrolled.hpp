@@ -46,7 +46,7 @@ namespace dmgs {
 // coefficients as the smoothing blocks do leaves this kernel 94 registers
 // short: 30 us for one workgroup.)  Bound by latency and by one CU's float64
 // arithmetic: 14 us for one workgroup, 17 us for 64 (32^3), 35 us at 64^3, where
-// eight half-sweep launches took 56 us (8^3: 25 us).
+// eight half-sweep launches took 56 us.
 struct UnBlockArgs {
     const double* ubar_in;
     double* ubar_out;                 // interior of the level (boundary entries are 0 in both)
