@@ -167,7 +167,8 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options *opt);
  * level).  Unset, the tuned defaults apply:
  *   DMGS_SWEEP2_MIN (64 / 16)   smallest N of the two-sweep streaming passes (float32 / float64 plans)
  *   DMGS_SWEEP2_WGS (256)       target workgroups of a finest-level two-sweep pass
- *   DMGS_SWEEP2_WGS_COARSE      ... below the finest level (half of the above)
+ *   DMGS_SWEEP2_WGS_COARSE      ... below the finest level (the above; half of it
+ *                               in the concurrent solves of dmgs_forward_vjp)
  *   DMGS_SWEEP2_DEFECT (2)      pre-smoothing pass writes the defect: 0 never, 1 from a zero iterate, 2 always
  *   DMGS_SWEEP2_FP64 (1)        float64 levels with a zero boundary use the two-sweep pass
  *   DMGS_SWEEP_CFG (0)          float32 one-sweep pass tiles: 0 16x64, 1 8x64, 2 16x32

@@ -636,7 +636,9 @@ int sweep2_grid(dmgs_plan P, SweepArgs<T>& a, int N, int TY, int TZ) {
     a.tiles_y = (N + TY - 1) / TY;
     a.tiles_z = (N + TZ - 1) / TZ;
     const int tiles = a.tiles_y * a.tiles_z;
-    const int wgs = N == P->lev[0].N ? P->cfg_sweep2_wgs : P->cfg_sweep2_wgs_coarse;
+    const int coarse = P->cfg_sweep2_wgs_coarse ? P->cfg_sweep2_wgs_coarse
+                                                : std::max(16, P->cfg_sweep2_wgs / (P->paired ? 2 : 1));
+    const int wgs = N == P->lev[0].N ? P->cfg_sweep2_wgs : coarse;
     int nch = std::max(1, (wgs + tiles - 1) / tiles);
     if (N == P->lev[0].N && P->cfg_sweep2_wgs == 256) {
         // finest level: one workgroup per CU, so pick the chunk count whose
@@ -2894,10 +2896,11 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     P->cfg_sweep2_min = kn.sweep2_min;
     P->cfg_sweep2_wgs = 256;
     if (const char* e = std::getenv("DMGS_SWEEP2_WGS")) P->cfg_sweep2_wgs = std::max(16, std::atoi(e));
-    // below the finest level the passes are latency-bound: longer chunks on
-    // half as many workgroups take less CU time, which the concurrent solves
-    // of dmgs_forward_vjp use
-    P->cfg_sweep2_wgs_coarse = std::max(16, P->cfg_sweep2_wgs / 2);
+    // below the finest level the passes are latency-bound: a solve on its own
+    // takes one workgroup per CU (512^3: 70.4 ms a step, 73.2 with half as
+    // many); the two concurrent solves of dmgs_forward_vjp take half each, as
+    // longer chunks cost less CU time (256^3 pair: 11.0 ms, 11.3 with 256)
+    P->cfg_sweep2_wgs_coarse = 0;
     if (const char* e = std::getenv("DMGS_SWEEP2_WGS_COARSE")) P->cfg_sweep2_wgs_coarse = std::max(16, std::atoi(e));
     if (const char* e = std::getenv("DMGS_SWEEP_CFG")) P->cfg_sweep = std::min(2, std::max(0, std::atoi(e)));
     // V(2,2) cycles run the block passes on every level (4096^2: 172 / 151 us a
@@ -3140,9 +3143,11 @@ int dmgs_forward_vjp(dmgs_plan P, const double* q, const double* rhobar, double*
     } else {
         HIPCHK(hipEventRecord(P->ev_fork, st));
         HIPCHK(hipStreamWaitEvent(P->twin_stream, P->ev_fork, 0));
+        P->paired = T->paired = true;
         std::thread adj(adjoint);
         sf = solve(P, q, rho, P->opt.bc_value, 0, info_fwd, st, nullptr, true);
         adj.join();
+        P->paired = T->paired = false;
     }
     if (hipEventRecord(P->ev_join, P->twin_stream) != hipSuccess || hipStreamWaitEvent(st, P->ev_join, 0) != hipSuccess) {
         set_error("event join failed");
