@@ -230,9 +230,44 @@ namespace {
 
 struct BatchGroup {
     const void* fn;
-    std::vector<const RecOp*> ops;
+    std::vector<RecOp*> ops;
     size_t off;
 };
+
+// Chunks of a group of two-sweep passes.  A request on its own cuts its march
+// into enough chunks to fill the CUs, and every chunk costs six steps more
+// than its planes; several requests fill them with longer ones.  One chunk
+// length for all, the one whose workgroups (one per CU at a time) take the
+// fewest steps: rounds of CUs times the length and those six (and about two
+// steps' worth of first loads).  The results do not depend on the chunks.
+// Two requests at 128^3 and two at 96^3: 95 us in chunks of 8 planes (four
+// rounds), 40 us in chunks of 26 (one).
+void batch_sweep_chunks(BatchGroup& g, int ncu) {
+    if (!g.ops[0]->sweep2 || g.ops.size() < 2) return;
+    std::vector<SweepArgs<float>> a(g.ops.size());
+    int longest = 8;
+    for (size_t i = 0; i < a.size(); i++) {
+        std::memcpy(&a[i], g.ops[i]->args, sizeof(a[i]));
+        longest = std::max(longest, a[i].N - 1);
+    }
+    int best = 0;
+    int64_t best_steps = INT64_MAX;
+    for (int c = 8; c <= longest; c++) {
+        int64_t nb = 0;
+        for (const auto& m : a) nb += (int64_t)m.tiles_y * m.tiles_z * ((m.N - 1 + c - 1) / c);
+        const int64_t steps = (nb + ncu - 1) / ncu * (c + 8);
+        if (steps < best_steps) {
+            best_steps = steps;
+            best = c;
+        }
+    }
+    for (size_t i = 0; i < a.size(); i++) {
+        a[i].chunk = std::min(a[i].N - 1, best);
+        a[i].nchunks = (a[i].N - 1 + a[i].chunk - 1) / a[i].chunk;
+        g.ops[i]->nblk = (unsigned)(a[i].tiles_y * a[i].tiles_z * a[i].nchunks);
+        std::memcpy(g.ops[i]->args, &a[i], sizeof(a[i]));
+    }
+}
 
 // Merge the requests' recorded launches into grouped launches and issue them.
 int batch_launch(dmgs_batch B, hipStream_t st) {
@@ -262,6 +297,7 @@ int batch_launch(dmgs_batch B, hipStream_t st) {
         for (BatchReq* r : live)
             if (r->next < r->ops.size() && r->ops[r->next].fn == best && (int)g.ops.size() < kGroupMax)
                 g.ops.push_back(&r->ops[r->next++]);
+        batch_sweep_chunks(g, live[0]->P->ncu);
         g.off = bytes;
         bytes += (g.ops[0]->table_bytes + 255) & ~(size_t)255;
         groups.push_back(std::move(g));

@@ -682,11 +682,13 @@ int launch_sweep2(dmgs_plan P, const SweepArgs<T>& a0, int N, int mode, hipStrea
         return DMGS_OK;
     }
     // grouped forms exist for the float32 passes (refinement plans)
-    auto go = [&](auto Mc) {
+    auto go = [&](auto Mc) -> int {
         constexpr int M = decltype(Mc)::value;
         const void* grp = nullptr;
         if constexpr (sizeof(T) == 4) grp = (const void*)k_rb_sweep2_grp<T, TY, TZ, M, HARM, DEFECT>;
-        return launch_rec(P, (const void*)k_rb_sweep2_col<T, TY, TZ, M, HARM, DEFECT>, grp, (unsigned)nb, NT, lds, a, st);
+        TRY(launch_rec(P, (const void*)k_rb_sweep2_col<T, TY, TZ, M, HARM, DEFECT>, grp, (unsigned)nb, NT, lds, a, st));
+        if (sizeof(T) == 4 && P->rec) P->rec->back().sweep2 = true;
+        return DMGS_OK;
     };
     if (mode == kSweepZero) return go(std::integral_constant<int, kSweepZero>());
     if (mode == kSweepPlain) return go(std::integral_constant<int, kSweepPlain>());

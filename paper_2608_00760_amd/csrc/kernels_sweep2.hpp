@@ -84,6 +84,12 @@ struct Sweep2Shape {
     static_assert(TY % 2 == 0 && TZ % 2 == 0, "even tile");
 };
 
+// Fused multiply-adds are written out where the compiler could fuse either
+// product: the steps of the unrolled march then round alike, and the results
+// do not depend on how a level's planes are cut into chunks.
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <class T>
 struct UD {
     T u, D;
@@ -272,13 +278,17 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
             // keeps 0/0 (outside the grid, D = 0) finite and changes no
             // rounding for D >= 1e-30
             auto hf = [&](T Da, T Db) { return (Da * Db) / ((Da + Db) + T(1.17549435e-38)) * a.st.two_inv_h2; };
-            num = (O ? P.q1 : P.q0) + hf(Di, Dxm) * uxm + hf(Di, Dxp) * uxp + hf(Di, ym.D) * ym.u + hf(Di, yp.D) * yp.u +
-                  hf(Di, Dzl) * uzl + hf(Di, Dzr) * uzr;
+            num = fma_(hf(Di, Dxm), uxm, O ? P.q1 : P.q0);
+            num = fma_(hf(Di, Dxp), uxp, num);
+            num = fma_(hf(Di, ym.D), ym.u, num);
+            num = fma_(hf(Di, yp.D), yp.u, num);
+            num = fma_(hf(Di, Dzl), uzl, num);
+            num = fma_(hf(Di, Dzr), uzr, num);
         } else {
             // arithmetic mean: c_ij = (D_i + D_j) / (2 h^2), the common factor applied once
-            const T s = ((Di + Dxm) * uxm + (Di + Dxp) * uxp) + ((Di + ym.D) * ym.u + (Di + yp.D) * yp.u) +
-                        ((Di + Dzl) * uzl + (Di + Dzr) * uzr);
-            num = (O ? P.q1 : P.q0) + s * a.st.half_inv_h2;
+            const T sx = fma_(Di + Dxm, uxm, (Di + Dxp) * uxp), sy = fma_(Di + ym.D, ym.u, (Di + yp.D) * yp.u);
+            const T sz = fma_(Di + Dzl, uzl, (Di + Dzr) * uzr);
+            num = fma_((sx + sy) + sz, a.st.half_inv_h2, O ? P.q1 : P.q0);
         }
         return num;
     };
@@ -340,7 +350,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
         const T num = gs_num(Oc, S4, Pb, Pm4, Pm3);
         // diagonal 1/w by the hardware reciprocal (1 ulp; the difference is
         // rounded in float32 anyway)
-        const T r = num - (O ? Pm4.u1 * __builtin_amdgcn_rcpf(Pm4.w1) : Pm4.u0 * __builtin_amdgcn_rcpf(Pm4.w0));
+        const T r = fma_(O ? -Pm4.u1 : -Pm4.u0, T(__builtin_amdgcn_rcpf(O ? Pm4.w1 : Pm4.w0)), num);
         const int po = s - 4;
         if (po >= xa && po < xb) buf_store<T>(O || in0 ? r : T(0), rR, roff + po * rplane_bytes);
     };

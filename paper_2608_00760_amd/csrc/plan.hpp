@@ -82,6 +82,7 @@ struct RecOp {
     unsigned nblk, threads;
     size_t lds;
     size_t table_bytes;
+    bool sweep2 = false;   // a float32 two-sweep pass: its chunks are chosen for the group
     void (*write)(unsigned char* dst, const RecOp* const* ops, int count, const int* start);
     alignas(16) unsigned char args[512];
 };

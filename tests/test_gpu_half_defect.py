@@ -31,3 +31,27 @@ def test_half_defect_restriction(N, face_mean, order, wgs, monkeypatch):
         # the tolerances of the float32 passes' own tests
         assert rel_max(host(gu), ru) <= 2e-5, (k, "pre u")
         assert np.abs(host(gqc) - rqc).max() <= 2e-5 * defect_scale(H, k, ru, q), (k, "pre qc")
+
+
+@pytest.mark.parametrize("precision,face_mean", [("fp32-in-fp64", "arith"), ("fp32-in-fp64", "harmonic"),
+                                                 ("fp64", "arith"), ("fp64", "harmonic")])
+@pytest.mark.parametrize("order", [0, 1])
+def test_results_do_not_depend_on_chunks(precision, face_mean, order, monkeypatch):
+    """Two-sweep passes cut into one, a few and many chunks: the same bits
+    (grouped execution chooses the chunks for the group)."""
+    import torch
+    from paper_2608_00760_amd import synth
+    N, fp32 = 96, precision != "fp64"
+    say("chunks %s %s order=%d" % (precision, face_mean, order))
+    monkeypatch.setenv("DMGS_SWEEP2_MIN", "32")
+    t = torch.float32 if fp32 else torch.float64
+    ref = None
+    for wgs in ("16", "40", "256"):
+        monkeypatch.setenv("DMGS_SWEEP2_WGS", wgs)
+        P, H = make(N, 7, precision=precision, face_mean=face_mean)
+        u, q, ec = (dev(synth.normal(n, i), t) for i, n in ((1, N), (2, N), (3, N // 2)))
+        got = [*P.debug_pre(0, u, q, order=order, fp32=fp32), P.debug_post(0, u, ec, q, order=order, fp32=fp32)]
+        if ref is None:
+            ref = got
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b), wgs
