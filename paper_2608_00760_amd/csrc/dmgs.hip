@@ -1039,7 +1039,7 @@ int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st, unsigned
         nb *= (unsigned)a.nt[x];
     }
     if (nb_out) *nb_out = nb;
-    if constexpr (MODE == kB3PreZero || MODE == kB3Pre || MODE == kB3Defect) {
+    if constexpr (MODE == kB3PreZero || MODE == kB3Pre || (MODE == kB3Defect && sizeof(T) == 8)) {
         if (coarse_behind<T>(P, k)) {
             if constexpr (sizeof(T) == 8)
                 if (P->grid) {
@@ -1105,13 +1105,13 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
         case kB3PreZero: TRY(go(std::integral_constant<int, kB3PreZero>())); break;
         case kB3Post: TRY(go(std::integral_constant<int, kB3Post>())); break;
         default:
-            if constexpr (sizeof(T) == 4) {
-                if (mode != kB3Pre) { set_error("internal: float32 block pass of mode %d", mode); return DMGS_ERR_INVALID; }
-                TRY(go(std::integral_constant<int, kB3Pre>()));
-            } else if (mode == kB3Sweep) {
+            if (mode == kB3Sweep) {
                 TRY(go(std::integral_constant<int, kB3Sweep>()));
             } else if (mode == kB3Defect) {
                 TRY(go(std::integral_constant<int, kB3Defect>()));
+            } else if constexpr (sizeof(T) == 4) {
+                if (mode != kB3Pre) { set_error("internal: float32 block pass of mode %d", mode); return DMGS_ERR_INVALID; }
+                TRY(go(std::integral_constant<int, kB3Pre>()));
             } else if (mode == kB3PostEpi && P->grid) {
                 a.ed = P->epi_d;
                 a.ew = P->epi_w;
@@ -1130,7 +1130,11 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
 template <class T>
 int block_pre(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int order, bool zero, hipStream_t st) {
     const T* none = nullptr;
-    if (zero || sizeof(T) == 4) {
+    // Float32 from an iterate: one pass over boxes of 20^3 when the coarse
+    // kernel runs behind it (32^3: 6.2 us), a sweep pass and a defect pass
+    // above that (64^3: 8.0 + 4.7 us for 16.7; where several solves share the
+    // GPU half the work, four requests 43 us for 74)
+    if (zero || (sizeof(T) == 4 && coarse_behind<T>(P, k))) {
         TRY(block_launch<T>(P, k, zero ? kB3PreZero : kB3Pre, *cur, *other, q, none, qc, order, st));
         std::swap(*cur, *other);
         return DMGS_OK;

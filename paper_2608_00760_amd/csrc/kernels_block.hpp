@@ -158,14 +158,15 @@ struct Block3 {
 // neighbour); the defect of a coarse vertex 2X needs u final two vertices
 // away.  Tiles are 8^3 with boxes of 16^3 (sweeps, correction), 18^3 (from
 // zero: tiles start at odd coordinates, so the box reaches 5 vertices on
-// either side) and 20^3 (float32 only: 1000 float64 blocks exceed the
-// registers of a CU, so float64 runs kB3Sweep and kB3Defect instead); the
-// defect's box of 16^3 gives 6^3 coarse vertices.
+// either side) and 20^3 (float32 with the coarse kernel behind it; other
+// levels, and float64, whose 1000 blocks exceed the registers of a CU, run
+// kB3Sweep and kB3Defect instead); the defect's box of 16^3 gives 6^3 coarse
+// vertices.
 //
 // Bound by latency (load, faces, four half-sweeps, store) and, from a few
 // workgroups per CU on, by the arithmetic of the whole box: 8 to 16 times
 // the tile's vertices, which is why larger levels march instead.  Measured
-// (pre- / post-smoothing): float32 64^3 16.7 / 8.3 us, 32^3 6.2 / 5.3 us (with
+// (pre- / post-smoothing): float32 64^3 8.0 + 4.7 / 8.3 us, 32^3 6.2 / 5.3 us (with
 // the fields in LDS and two coefficients read per neighbour 21.3 / 13.9 and
 // 9.6 / 8.8 us); float64 48^3 9.3 / 7.4 us, 24^3 7.7 / 7.0 us (marching passes
 // with the separate restriction 24 / 21 and 22 / 20 us); the paper's
