@@ -1093,7 +1093,8 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
     const bool h = harmonic(P);
     // algorithmic bytes: q, D, w, and u read unless zero, u written, plus the
     // coarse level's share
-    const double words = (mode == kB3PreZero ? 4.0 : mode == kB3Defect ? 4.0 : 5.0) + (mode == kB3Sweep ? 0.0 : 0.125);
+    const double words = (mode == kB3Sweep || mode == kB3Pre ? 5.0 : 4.0) + (mode == kB3Sweep || mode == kB3Zero ? 0.0 : 0.125) +
+                         (mode == kB3Post || mode == kB3PostEpi ? 1.0 : 0.0);
     const int cls = mode == kB3Defect ? DMGS_K_DEFECT_RESTRICT : DMGS_K_SMOOTH;
     int slot;
     TRY(tbeg(P, k, st, &slot, cls));
@@ -1110,8 +1111,9 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
             } else if (mode == kB3Defect) {
                 TRY(go(std::integral_constant<int, kB3Defect>()));
             } else if constexpr (sizeof(T) == 4) {
-                if (mode != kB3Pre) { set_error("internal: float32 block pass of mode %d", mode); return DMGS_ERR_INVALID; }
-                TRY(go(std::integral_constant<int, kB3Pre>()));
+                if (mode == kB3Pre) TRY(go(std::integral_constant<int, kB3Pre>()));
+                else if (mode == kB3Zero) TRY(go(std::integral_constant<int, kB3Zero>()));
+                else { set_error("internal: float32 block pass of mode %d", mode); return DMGS_ERR_INVALID; }
             } else if (mode == kB3PostEpi && P->grid) {
                 a.ed = P->epi_d;
                 a.ew = P->epi_w;
@@ -1130,16 +1132,21 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
 template <class T>
 int block_pre(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int order, bool zero, hipStream_t st) {
     const T* none = nullptr;
-    // Float32 from an iterate: one pass over boxes of 20^3 when the coarse
-    // kernel runs behind it (32^3: 6.2 us), a sweep pass and a defect pass
-    // above that (64^3: 8.0 + 4.7 us for 16.7; where several solves share the
-    // GPU half the work, four requests 43 us for 74)
-    if (zero || (sizeof(T) == 4 && coarse_behind<T>(P, k))) {
+    // One pass with the coarse kernel behind it; from zero also for float64
+    // (64^3: 19 us, 13.5 + 7.5 as two passes) and up to 48^3 (7.2 us for 5.0 +
+    // 5.0).  Larger float32 boxes of 18^3 and 20^3 cost more than a sweep pass
+    // over boxes of 16^3 and a defect pass: 64^3 from zero 13.7 us for 7.6 +
+    // 4.8, from an iterate 16.7 for 8.0 + 4.7; where several solves share the
+    // GPU, by half (four requests: 74 us for 43), so that grouped execution
+    // takes two passes at 48^3 too; the forms round alike.  (One pass there
+    // also put requests at 96^3 and 128^3 out of step: 15.3 ms for 12.2.)
+    const bool one = coarse_behind<T>(P, k) || P->grid || (zero && (sizeof(T) == 8 || (P->lev[k].N <= 48 && !P->rec)));
+    if (one && (zero || sizeof(T) == 4)) {
         TRY(block_launch<T>(P, k, zero ? kB3PreZero : kB3Pre, *cur, *other, q, none, qc, order, st));
         std::swap(*cur, *other);
         return DMGS_OK;
     }
-    TRY(block_launch<T>(P, k, kB3Sweep, *cur, *other, q, none, (T*)nullptr, order, st));
+    TRY(block_launch<T>(P, k, zero ? kB3Zero : kB3Sweep, *cur, *other, q, none, (T*)nullptr, order, st));
     std::swap(*cur, *other);
     return block_launch<T>(P, k, kB3Defect, *cur, (T*)nullptr, q, none, qc, order, st);
 }

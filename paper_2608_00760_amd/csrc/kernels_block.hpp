@@ -144,6 +144,8 @@ struct Block3 {
 // around it (the box) as NB^3 blocks of one thread each.
 //   kB3PreZero  two red-black sweeps from zero, u and the restricted defect
 //   kB3Pre      the same from u_in
+//   kB3Zero     two sweeps from zero, u only (float32; tiles of 10^3, starting
+//               at odd coordinates, in boxes of 16^3)
 //   kB3Sweep    two sweeps from u_in, u only; optionally (a.partial) the
 //               squared residual of u_in on the tile's first colour
 //   kB3Defect   the restricted defect of u_in, whose last half-sweep updated
@@ -174,7 +176,7 @@ struct Block3 {
 //   kB3PostEpi  kB3Post on a general grid, with the likelihood epilogue of
 //               the result: rhobar = mua w (mua u - d) (0 on the boundary)
 //               and per-workgroup sums of w (mua u - d)^2 and of w > 0
-enum Block3Mode { kB3PreZero = 0, kB3Pre = 1, kB3Sweep = 2, kB3Defect = 3, kB3Post = 4, kB3PostEpi = 5 };
+enum Block3Mode { kB3PreZero = 0, kB3Pre = 1, kB3Sweep = 2, kB3Defect = 3, kB3Post = 4, kB3PostEpi = 5, kB3Zero = 6 };
 
 template <class T>
 struct Block3Args {
@@ -199,9 +201,10 @@ struct Block3Args {
 template <int MODE, bool GEN>
 struct Block3Shape {
     static constexpr int NB = MODE == kB3PreZero ? 9 : MODE == kB3Pre ? 10 : 8;     // blocks per axis
-    static constexpr int TILE = MODE == kB3Defect ? 12 : 8;                          // fine vertices per tile and axis
-    static constexpr int ORG = MODE == kB3Pre ? -6 : MODE == kB3Defect ? 0 : -4;     // box origin from TILE * tile
-    static constexpr int LO = MODE == kB3PreZero ? 5 : MODE == kB3Pre ? 6 : 4;       // tile in the box
+    static constexpr int TILE = MODE == kB3Defect ? 12 : MODE == kB3Zero ? 10 : 8;   // fine vertices per tile and axis
+    static constexpr int ORG = MODE == kB3Pre ? -6 : MODE == kB3Defect ? 0 : MODE == kB3Zero ? -2 : -4;   // box origin from TILE * tile
+    static constexpr int LO = MODE == kB3PreZero ? 5 : MODE == kB3Pre ? 6 : MODE == kB3Zero ? 3 : 4;      // tile in the box
+    static constexpr int HI = LO + (MODE == kB3Zero ? 10 : 8);
     static constexpr int CLO = MODE == kB3Defect ? 1 : 3, CHI = 7;                   // blocks whose corners are restricted to
     // general grids form w from the faces, which a sweep from zero needs on
     // the box's last vertices too: D one vertex past them, in a pad
@@ -209,7 +212,9 @@ struct Block3Shape {
     static constexpr int Y = NB + EDGE, X = Y * Y, S = X * Y;
     static constexpr int NT = (NB * NB * NB + 63) / 64 * 64;
     __host__ static int tiles(int N) {
-        return MODE == kB3PreZero ? (N - 1 + 7) / 8 : MODE == kB3Defect ? std::max(1, (N / 2 - 1 + 5) / 6) : (N + 7) / 8;
+        return MODE == kB3PreZero || MODE == kB3Zero ? (N - 1 + TILE - 1) / TILE
+               : MODE == kB3Defect                     ? std::max(1, (N / 2 - 1 + 5) / 6)
+                                                       : (N + 7) / 8;
     }
 };
 
@@ -222,6 +227,7 @@ template <class T, int MODE, bool HARM, bool GEN, bool COHERENT = false, bool TA
 __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bid) {
     using Sh = Block3Shape<MODE, GEN>;
     constexpr int NB = Sh::NB, S = Sh::S, X = Sh::X, Y = Sh::Y;
+    constexpr bool ZERO = MODE == kB3PreZero || MODE == kB3Zero;
     extern __shared__ __align__(16) unsigned char block_smem[];
     T* const base = reinterpret_cast<T*>(block_smem);
     using B3 = Block3<T, S, X, Y>;
@@ -243,7 +249,7 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
         for (int k = 0; k < 2; k++) {
             in[ax][k] = g[ax] + k >= 0 && g[ax] + k <= a.n[ax];
             inner[ax][k] = g[ax] + k > 0 && g[ax] + k < a.n[ax];
-            tile[ax][k] = l3[ax] + k >= Sh::LO && l3[ax] + k < Sh::LO + 8;
+            tile[ax][k] = l3[ax] + k >= Sh::LO && l3[ax] + k < Sh::HI;
         }
     auto of = [](const bool (&f)[3][2], int o) { return f[0][o >> 2] && f[1][(o >> 1) & 1] && f[2][o & 1]; };
 
@@ -272,7 +278,7 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
         load(a.D, D);
         load(a.w, P.w);
         load(a.q, P.q);
-        if (MODE != kB3PreZero) load(a.u_in, P.u);
+        if (!ZERO) load(a.u_in, P.u);
         if (Sh::EDGE) {
             const int l[3] = {lx, ly, lz};
 #pragma unroll
@@ -316,7 +322,7 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
             if (GEN) P.w[o] = T(1) / P.diag(o, P.w[o]);
             P.w[o] = of(inner, o) ? P.w[o] : T(0);
             P.q[o] = of(in, o) ? P.q[o] : T(0);
-            if (MODE == kB3PreZero) P.u[o] = of(inner, o) && B3::colour(o) == a.order ? P.w[o] * P.q[o] : T(0);
+            if (ZERO) P.u[o] = of(inner, o) && B3::colour(o) == a.order ? P.w[o] * P.q[o] : T(0);
             else P.u[o] = of(in, o) ? P.u[o] : T(0);
         }
         __syncthreads();
@@ -348,7 +354,7 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
         };
         if (TAPE && MODE == kB3PreZero) store(a.tape);
         // the first half-sweep from zero was u = w q
-        for (int j = MODE == kB3PreZero ? 1 : 0; j < 4; j++) {
+        for (int j = ZERO ? 1 : 0; j < 4; j++) {
             if (act) {
                 if ((j & 1) ? !a.order : a.order) P.template half<1, true>(base, idx);
                 else P.template half<0, true>(base, idx);

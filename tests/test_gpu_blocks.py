@@ -76,3 +76,18 @@ def test_norm_from_the_next_sweeps(cells):
         assert info["rel_residual"] <= 1e-10
         assert abs(rel - info["rel_residual"]) <= 1e-3 * info["rel_residual"]
     P.close()
+
+
+@pytest.mark.parametrize("face_mean", ["arith", "harmonic"])
+def test_grouped_48_rounds_like_alone(face_mean):
+    """Levels of 48 cells pre-smooth from zero in one pass alone and in two in
+    grouped execution: the same bits, as every grouped request's."""
+    import test_gpu_batch as batch
+    from paper_2608_00760_amd.solver import Batch
+    say("grouped 48^3 %s" % face_mean)
+    B, reqs = Batch(), {}
+    for tag, mode in enumerate(("vjp", "jvp")):
+        P, c, t = batch.make_plan(96, 5 + tag, face_mean=face_mean)
+        reqs[tag] = (P, c, t, mode)
+        batch.add(B, P, c, t, mode, tag)
+    batch.check_against_solo(reqs, B.run())
