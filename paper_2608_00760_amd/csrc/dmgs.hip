@@ -661,16 +661,15 @@ int sweep2_grid(dmgs_plan P, SweepArgs<T>& a, int N, int TY, int TZ) {
     return tiles * a.nchunks;
 }
 
-// NORM: a plain pass that also leaves the per-block sums of its input's
-// squared residual in a.partial (*nb_out blocks).
+// NORM: a plain pass that also leaves its input's squared residual norm in
+// a.norm.
 template <class T, int TY, int TZ, bool HARM, bool DEFECT, bool NORM = false>
-int launch_sweep2(dmgs_plan P, const SweepArgs<T>& a0, int N, int mode, hipStream_t st, unsigned* nb_out = nullptr) {
+int launch_sweep2(dmgs_plan P, const SweepArgs<T>& a0, int N, int mode, hipStream_t st) {
     SweepArgs<T> a = a0;
     constexpr int RING = DEFECT ? 5 : 4;
     constexpr int NT = Sweep2Shape<TY, TZ, RING>::NT;
     constexpr size_t lds = sweep2_lds_bytes<T, TY, TZ, RING>();
     const int nb = sweep2_grid<T>(P, a, N, TY, TZ);
-    if (nb_out) *nb_out = (unsigned)nb;
     if constexpr (NORM) {
         if (mode != kSweepPlain || nb > kMaxPartials || !a.partial) {
             set_error("internal: two-sweep norm pass needs a plain pass of at most %d workgroups", kMaxPartials);
@@ -758,11 +757,11 @@ bool use_sweep2(dmgs_plan P, int k, size_t tsize) {
 
 // One two-sweep pass: u_out = two red-black sweeps applied to u_in (or to
 // 0, or to u_in + I ec).
-// norm_partial (float64, plain passes): also the per-block sums of the
-// input's squared residual there (*nb_out blocks).
+// norm_slot (float64, plain passes): also the input's squared residual norm,
+// into that slot of the norms.
 template <class T>
 int smooth_pass2(dmgs_plan P, int k, const T* u_in, T* u_out, const T* q, int order, bool zero, const T* ec,
-                 hipStream_t st, T* r = nullptr, double* norm_partial = nullptr, unsigned* nb_out = nullptr) {
+                 hipStream_t st, T* r = nullptr, int norm_slot = -1) {
     const Level& l = P->lev[k];
     SweepArgs<T> a;
     a.u_in = u_in;
@@ -779,7 +778,7 @@ int smooth_pass2(dmgs_plan P, int k, const T* u_in, T* u_out, const T* q, int or
     a.st = l.stencil<T>(harmonic(P));
     const int mode = zero ? kSweepZero : (ec ? kSweepProlong : kSweepPlain);
     if (r && ec) { set_error("two-sweep pass: defect only after pre-smoothing"); return DMGS_ERR_INVALID; }
-    if (norm_partial && (sizeof(T) != 8 || zero || ec || r)) {
+    if (norm_slot >= 0 && (sizeof(T) != 8 || zero || ec || r)) {
         set_error("internal: the two-sweep norm pass is a plain float64 pass");
         return DMGS_ERR_INVALID;
     }
@@ -797,10 +796,12 @@ int smooth_pass2(dmgs_plan P, int k, const T* u_in, T* u_out, const T* q, int or
         // float64: half-width tiles (the LDS ring holds twice the bytes);
         // no defect-writing variant
         if (r) { set_error("two-sweep pass: no defect output in float64"); return DMGS_ERR_INVALID; }
-        if (norm_partial) {
-            a.partial = norm_partial;
-            TRY(harmonic(P) ? (launch_sweep2<T, kSweep2TY, kSweep2TZ64, true, false, true>(P, a, l.N, mode, st, nb_out))
-                            : (launch_sweep2<T, kSweep2TY, kSweep2TZ64, false, false, true>(P, a, l.N, mode, st, nb_out)));
+        if (norm_slot >= 0) {
+            a.partial = P->partial;
+            a.norm = norm_dst(P) + norm_slot;
+            a.done = reinterpret_cast<unsigned*>(P->dflag + 1);
+            TRY(harmonic(P) ? (launch_sweep2<T, kSweep2TY, kSweep2TZ64, true, false, true>(P, a, l.N, mode, st))
+                            : (launch_sweep2<T, kSweep2TY, kSweep2TZ64, false, false, true>(P, a, l.N, mode, st)));
         } else {
             TRY(harmonic(P) ? (launch_sweep2<T, kSweep2TY, kSweep2TZ64, true, false>(P, a, l.N, mode, st))
                             : (launch_sweep2<T, kSweep2TY, kSweep2TZ64, false, false>(P, a, l.N, mode, st)));
@@ -1028,8 +1029,21 @@ int launch_block_tail(dmgs_plan P, int k, const Block3Args<T>& b, unsigned nb, h
                       block_tail_lds<T, MODE, GEN>(), a, st);
 }
 
+// Workgroups (and norm partials) of a kB3Sweep launch on level k.
+int64_t block_sweep_blocks(dmgs_plan P, int k) {
+    int64_t nb = 1;
+    for (int x = 0; x < 3; x++) nb *= Block3Shape<kB3Sweep, false>::tiles(P->lev[k].nc[x]);
+    return nb;
+}
+
+// A norm's parts are added up by the launch's last workgroup while about one
+// round of workgroups counts itself (32^3, 64 of them: 77 us less in a solve
+// and pull-back of 1.5 ms); with more the counting itself takes longer than a
+// launch for the sum (1024: 34.5 us for 29 + 4).
+constexpr int64_t kSumArrivedMax = 256;
+
 template <class T, int MODE, bool HARM>
-int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st, unsigned* nb_out) {
+int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st) {
     const Level& l = P->lev[k];
     unsigned nb = 1;
     for (int x = 0; x < 3; x++) {
@@ -1038,7 +1052,6 @@ int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st, unsigned
         a.nt[x] = Block3Shape<MODE, false>::tiles(l.nc[x]);
         nb *= (unsigned)a.nt[x];
     }
-    if (nb_out) *nb_out = nb;
     if constexpr (MODE == kB3PreZero || MODE == kB3Pre || (MODE == kB3Defect && sizeof(T) == 8)) {
         if (coarse_behind<T>(P, k)) {
             if constexpr (sizeof(T) == 8)
@@ -1073,11 +1086,11 @@ int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st, unsigned
 }
 
 // One block launch on level k (Block3Mode): u_in, u_out, the correction ec
-// and the restricted defect qc as the mode takes them; kB3Sweep with partial
-// also sums the squares of u_in's residual per workgroup (*nb_out of them).
+// and the restricted defect qc as the mode takes them; kB3Sweep with norm_slot
+// also sums the squares of u_in's residual there.
 template <class T>
 int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T* q, const T* ec, T* qc, int order,
-                 hipStream_t st, double* partial = nullptr, unsigned* nb_out = nullptr) {
+                 hipStream_t st, int norm_slot = -1) {
     const Level& l = P->lev[k];
     if (!P->grid) TRY(need_dense<T>(P, k, "block pass"));
     Block3Args<T> a{};
@@ -1088,7 +1101,12 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
     a.w = Typed<T>::w(l);
     a.ec = ec;
     a.qc = qc;
-    a.partial = partial;
+    const int64_t parts = norm_slot >= 0 ? block_sweep_blocks(P, k) : 0;
+    if (parts) {
+        a.partial = P->partial;
+        a.norm = norm_dst(P) + norm_slot;
+        if (parts <= kSumArrivedMax) a.done = reinterpret_cast<unsigned*>(P->dflag + 1);
+    }
     a.order = order;
     const bool h = harmonic(P);
     // algorithmic bytes: q, D, w, and u read unless zero, u written, plus the
@@ -1100,7 +1118,7 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
     TRY(tbeg(P, k, st, &slot, cls));
     auto go = [&](auto Mc) -> int {
         constexpr int M = decltype(Mc)::value;
-        return h ? launch_block3<T, M, true>(P, k, a, st, nb_out) : launch_block3<T, M, false>(P, k, a, st, nb_out);
+        return h ? launch_block3<T, M, true>(P, k, a, st) : launch_block3<T, M, false>(P, k, a, st);
     };
     switch (mode) {
         case kB3PreZero: TRY(go(std::integral_constant<int, kB3PreZero>())); break;
@@ -1115,6 +1133,7 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
                 else if (mode == kB3Zero) TRY(go(std::integral_constant<int, kB3Zero>()));
                 else { set_error("internal: float32 block pass of mode %d", mode); return DMGS_ERR_INVALID; }
             } else if (mode == kB3PostEpi && P->grid) {
+                a.partial = P->partial;
                 a.ed = P->epi_d;
                 a.ew = P->epi_w;
                 a.rhobar = P->epi_rhobar;
@@ -1124,7 +1143,13 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
                 return DMGS_ERR_INVALID;
             }
     }
-    return tend(P, slot, cls, words * l.nv * sizeof(T), st);
+    TRY(tend(P, slot, cls, words * l.nv * sizeof(T), st));
+    if (parts > kSumArrivedMax) {
+        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial, (int)parts, norm_dst(P),
+                           norm_slot);
+        LAUNCHCHK();
+    }
+    return DMGS_OK;
 }
 
 // Pre-smoothing phase of a block level from *cur (or from zero), qc = R (q -
@@ -1149,13 +1174,6 @@ int block_pre(dmgs_plan P, int k, T** cur, T** other, const T* q, T* qc, int ord
     TRY(block_launch<T>(P, k, zero ? kB3Zero : kB3Sweep, *cur, *other, q, none, (T*)nullptr, order, st));
     std::swap(*cur, *other);
     return block_launch<T>(P, k, kB3Defect, *cur, (T*)nullptr, q, none, qc, order, st);
-}
-
-// Workgroups (and norm partials) of a kB3Sweep launch on level k.
-int64_t block_sweep_blocks(dmgs_plan P, int k) {
-    int64_t nb = 1;
-    for (int x = 0; x < 3; x++) nb *= Block3Shape<kB3Sweep, false>::tiles(P->lev[k].nc[x]);
-    return nb;
 }
 
 // Post-smoothing phase: u = *cur + I ec, two sweeps.
@@ -1781,8 +1799,8 @@ int vcycle_grid(dmgs_plan P, int k, double* u, const double* q, int order, hipSt
 int post_grid_blocks(dmgs_plan P, double** cur, double** other, const double* q, const double* ec, int order,
                      hipStream_t st, bool epi) {
     if (!epi) return block_post<double>(P, 0, cur, other, q, ec, order, st);
-    unsigned nb = 0;
-    TRY(block_launch<double>(P, 0, kB3PostEpi, *cur, *other, q, ec, nullptr, order, st, P->partial, &nb));
+    const int64_t nb = block_sweep_blocks(P, 0);   // the same tiles
+    TRY(block_launch<double>(P, 0, kB3PostEpi, *cur, *other, q, ec, nullptr, order, st));
     std::swap(*cur, *other);
     for (int i = 0; i < 2; i++) {
         hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial + i * nb, (int)nb,
@@ -1877,12 +1895,8 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
             bool done = false;
             if (free_norm && cycles >= 2) {
                 double* prev = cur;
-                unsigned nb = 0;
-                TRY(block_launch<double>(P, 0, kB3Sweep, cur, oth, b, nullptr, nullptr, order, st, P->partial, &nb));
+                TRY(block_launch<double>(P, 0, kB3Sweep, cur, oth, b, nullptr, nullptr, order, st, 1));
                 std::swap(cur, oth);
-                hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial, (int)nb,
-                                   norm_dst(P), 1);
-                LAUNCHCHK();
                 TRY(mark_norms(P, st));
                 const Level& c1 = P->lev[1];
                 TRY(block_launch<double>(P, 0, kB3Defect, cur, nullptr, b, nullptr, c1.q64, order, st));
@@ -2024,13 +2038,9 @@ int solve(dmgs_plan P, const double* b, double* x, double bc, int order, dmgs_in
             if (free_norm && cycles >= 2) {
                 // cycle `cycles` from u_{cycles-1} (in cur)
                 double* prev = cur;
-                unsigned nb = 0;
-                if (blocks) TRY(block_launch<double>(P, 0, kB3Sweep, cur, oth, b, nullptr, nullptr, order, st, P->partial, &nb));
-                else TRY(smooth_pass2<double>(P, 0, cur, oth, b, order, false, nullptr, st, nullptr, P->partial, &nb));
+                if (blocks) TRY(block_launch<double>(P, 0, kB3Sweep, cur, oth, b, nullptr, nullptr, order, st, 1));
+                else TRY(smooth_pass2<double>(P, 0, cur, oth, b, order, false, nullptr, st, nullptr, 1));
                 std::swap(cur, oth);
-                hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, (const double*)P->partial, (int)nb,
-                                   norm_dst(P), 1);
-                LAUNCHCHK();
                 TRY(mark_norms(P, st));
                 if (nu_pre_of(P, order) > 2)
                     TRY(smooth_phase<double>(P, 0, &cur, &oth, b, nu_pre_of(P, order) - 2, order, false, (const double*)nullptr, st));

@@ -390,6 +390,33 @@ __global__ void k_sum_partials(const double* __restrict__ partial, int count, do
     if (threadIdx.x == 0) out[slot] = b;
 }
 
+// The same sum by the last of a launch's nb workgroups to arrive here, instead
+// of a launch of its own (4 us and a gap between two passes of 8 to 19 us):
+// every workgroup stores its part past the caches, waits for the store and
+// counts itself; the one that counts to nb reads the parts past the caches.
+// No release or acquire: nothing but the parts is handed over, and they pass
+// no cache (a release per workgroup writes the L2 back, 1024 times a launch).
+// *done is 0 before the launch and after it.  b: this workgroup's part, on
+// thread 0; every thread of the workgroup calls.
+__device__ __forceinline__ void sum_arrived(double b, double* partial, int bid, unsigned nb, unsigned* done, double* out) {
+    __shared__ unsigned order;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(partial + bid, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        order = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (order != nb - 1) return;
+    double acc = 0.0;
+    for (unsigned i = threadIdx.x; i < nb; i += blockDim.x)
+        acc += __hip_atomic_load(partial + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double sum = block_sum(acc);
+    if (threadIdx.x == 0) {
+        *out = sum;
+        __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // Arguments of k_sum_partials; grouped form, one workgroup per member (the
 // same sums, in the same order).
 struct SumArgs {

@@ -147,7 +147,7 @@ struct Block3 {
 //   kB3Zero     two sweeps from zero, u only (float32; tiles of 10^3, starting
 //               at odd coordinates, in boxes of 16^3)
 //   kB3Sweep    two sweeps from u_in, u only; optionally (a.partial) the
-//               squared residual of u_in on the tile's first colour
+//               squared residual of u_in, on the tile's first colour
 //   kB3Defect   the restricted defect of u_in, whose last half-sweep updated
 //               the second colour
 //   kB3Post     u_in plus the trilinear correction, two sweeps, u
@@ -188,6 +188,8 @@ struct Block3Args {
     const T* ec;       // coarse correction (kB3Post)
     T* qc;             // restricted defect (coarse interior written)
     double* partial;   // per-workgroup sums: kB3Sweep of squares (or null); kB3PostEpi two a workgroup, by kind
+    double* norm;      // kB3Sweep with partial: their sum, by the last workgroup ...
+    unsigned* done;    // ... counted here (null: not summed)
     int n[3];          // cells per axis
     int nt[3];         // tiles per axis
     T s[3];            // per axis: 1 / (2 h^2) or 2 / h^2 (harmonic)
@@ -333,6 +335,7 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
         if (a.order) P.template residual<1>(base, idx, r);
         else P.template residual<0>(base, idx, r);
     };
+    double part = 0.0;
     if (MODE == kB3Sweep && a.partial) {
         double acc = 0.0;
         if (act) {
@@ -341,8 +344,7 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
 #pragma unroll
             for (int o = 0; o < 8; o++) acc += of(tile, o) ? (double)r[o] * (double)r[o] : 0.0;
         }
-        const double sum = block_sum(acc);
-        if (tid == 0) a.partial[bid] = sum;
+        part = block_sum(acc);
     }
     if (MODE != kB3Defect) {
         auto store = [&](T* out) {
@@ -363,6 +365,10 @@ __device__ __forceinline__ void block3_body(const Block3Args<T>& a, const int bi
             __syncthreads();
         }
         if (!TAPE) store(a.u_out);
+    }
+    if (MODE == kB3Sweep && a.partial) {
+        if (a.done) sum_arrived(part, a.partial, bid, (unsigned)(a.nt[0] * a.nt[1] * a.nt[2]), a.done, a.norm);
+        else if (tid == 0) a.partial[bid] = part;
     }
     if constexpr (MODE == kB3PostEpi) {
         double acc = 0.0, cnt = 0.0;

@@ -103,6 +103,8 @@ struct SweepArgs {
     const T* ec;     // coarse correction added by prolongation (MODE 2)
     T* r;            // defect of the result's first colour, one value a pair (two-sweep passes with DEFECT)
     double* partial = nullptr;   // per-block sums of the input's squared residual (two-sweep passes with NORM)
+    double* norm = nullptr;      // ... their sum, by the last workgroup
+    unsigned* done = nullptr;    // ... workgroups that have stored theirs
     // layout of u_in, u_out, q, D and w (two-sweep passes): vertex (x, y, z) at
     // x px + y py + z (r: half_pitch); the one-sweep pass takes dense fields
     int py = 0;

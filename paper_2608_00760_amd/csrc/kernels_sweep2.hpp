@@ -60,7 +60,7 @@
 // u_j from the input, and the residual is that minus u_i / w_i.  When the
 // input ended a red-black sweep whose last colour is this pass's second,
 // the second colour's residual is 0 (up to rounding), so the block sums
-// (one per workgroup, in a.partial) add up to ||q - A u||^2 of the input.
+// (one per workgroup, in a.partial) add up to ||q - A u||^2 of the input; the last workgroup adds them up.
 #pragma once
 #include "kernels_stream.hpp"
 
@@ -443,8 +443,7 @@ __device__ __forceinline__ void rb_sweep2_body(const SweepArgs<T>& a, const int 
         step(I7(), s + 7, R7, R0, R1, R2, R3, R4, R6);
     }
     if constexpr (NORM) {
-        const double b = block_sum(nacc);
-        if (tid == 0) a.partial[bid] = b;
+        sum_arrived(block_sum(nacc), a.partial, bid, (unsigned)nb, a.done, a.norm);
     }
 }
 
