@@ -2696,16 +2696,6 @@ int kernel_attributes(int device) {
     return DMGS_OK;
 }
 
-// Levels, buffers and configuration of a new plan on the current device.
-// Ordinary plans allocate every buffer (hipMalloc, pinned host slots,
-// events) and clear the work buffers synchronously; arena plans (P->arena
-// set) carve the buffers from the arena and clear them with fill kernels on
-// stream zst.  On failure the caller frees what was allocated (free_plan).
-// Levels and buffers of a general-grid plan (see plan_init): per level
-// D64, mu64, below the finest u64 and q64, above the coarsest t64 (the
-// defect); the finest scratch, partials, the coarsest inverse, the flag.
-int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst);
-
 // The validation flag and the count of finished workgroups, both 0.
 int clear_flags(dmgs_plan P, hipStream_t zst) {
     TRY(dalloc(P, &P->dflag, 2));
@@ -2718,6 +2708,9 @@ int clear_flags(dmgs_plan P, hipStream_t zst) {
     return DMGS_OK;
 }
 
+// Levels and buffers of a general-grid plan (see plan_init): per level
+// D64, mu64, below the finest u64 and q64, above the coarsest t64 (the
+// defect); the finest scratch, partials, the coarsest inverse, the flag.
 int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     P->grid = true;
     // the one tuning knob that applies to general grids
@@ -2793,6 +2786,11 @@ int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     return st;
 }
 
+// Levels, buffers and configuration of a new plan on the current device.
+// Ordinary plans allocate every buffer (hipMalloc, pinned host slots,
+// events) and clear the work buffers synchronously; arena plans (P->arena
+// set) carve the buffers from the arena and clear them with fill kernels on
+// stream zst.  On failure the caller frees what was allocated (free_plan).
 int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     P->opt = *o;
     if (hipGetDevice(&P->device) != hipSuccess) { (void)hipGetLastError(); set_error("hipGetDevice failed"); return DMGS_ERR_HIP; }

@@ -24,10 +24,16 @@
 // (its update solved its own equations), so only the other colour's is
 // formed and restricted.
 //
-// Measured, 16^3 .. 2^3 levels, V(2,2): float32 25 -> 15 us per call,
-// float64 18 us, where the 16^3 level took three launches of its own (pass,
+// From the first level of at most 64 unknowns down the whole cycle is linear
+// in its right-hand side: one matrix, formed once per coefficient set
+// (k_small_cols), and one product per call (15 -> 12.6 us).
+//
+// Measured, 16^3 .. 2^3 levels, V(2,2): float32 25 -> 12.6 us per call,
+// float64 15.3 us, where the 16^3 level took three launches of its own (pass,
 // restriction, pass: 42 us) before an 11 us call for the levels below it;
-// of a 12^3 level the same cost 12 launches of one operation each.
+// of a 12^3 level the same cost 12 launches of one operation each.  As the
+// last workgroup of the restricting pass over 32^3 (BlockTailArgs), which
+// hides its loads: 16.8 and 18.6 us for both.
 #pragma once
 #include "grid.hpp"
 #include "kernels_basic.hpp"
