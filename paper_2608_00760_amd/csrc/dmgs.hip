@@ -1079,6 +1079,9 @@ int launch_block3(dmgs_plan P, int k, Block3Args<T>& a, hipStream_t st) {
         }
         LAUNCHCHK();
         return DMGS_OK;
+    } else if constexpr (MODE == kB3Pre) {
+        set_error("internal: float32 levels without the coarse kernel behind them sweep and restrict in two passes");
+        return DMGS_ERR_INVALID;
     } else {
         return launch_rec(P, (const void*)k_block3<T, MODE, HARM, false>, (const void*)k_block3_grp<T, MODE, HARM>, nb,
                           Block3Shape<MODE, false>::NT, block3_lds<T, MODE, false>(), a, st);
