@@ -285,6 +285,17 @@ int64_t tail_entries(const dmgs_options* o) {
     return m * m;
 }
 
+// Entries of the reductions' partials.  The block passes over a general grid's
+// finest level leave one sum a tile (the norm) or two (the likelihood's
+// epilogue, which arena plans never take: they keep the other reductions'
+// count, and past that many tiles the norm's own pass).
+int64_t partial_entries(const dmgs_options* o, bool arena) {
+    if (arena || !general_grid(o)) return kMaxPartials;
+    int64_t tiles = 1;
+    for (int a = 0; a < 3; a++) tiles *= Block3Shape<kB3Sweep, false>::tiles(o->n[a]);
+    return std::max<int64_t>(kMaxPartials, 2 * tiles);
+}
+
 // arena: without the coarse cycle's matrix and the second flag word (at most
 // 33 KB), which the slack of an arena plan holds.
 size_t footprint(const dmgs_options* o, bool arena = false) {
@@ -298,8 +309,8 @@ size_t footprint(const dmgs_options* o, bool arena = false) {
         for (int k = 0; k < s.L; k++)
             b += (2 + (k > 0 ? 2 : 0) + (k < s.L - 1 ? 1 : 0)) * s.nv[k] * sizeof(double);
         b += s.nv[0] * sizeof(double);
-        b += kMaxPartials * sizeof(double) + kGridCoarseMax * kGridCoarseMax * sizeof(double) + 4 * sizeof(double) +
-             (arena ? 1 : 2) * sizeof(int);
+        b += partial_entries(o, arena) * sizeof(double) + kGridCoarseMax * kGridCoarseMax * sizeof(double) +
+             4 * sizeof(double) + (arena ? 1 : 2) * sizeof(int);
         return b + (arena ? 0 : tail_entries(o) * sizeof(double));
     }
     const int py0 = fine_row_pitch(o, read_knobs(o), s.L);
@@ -1886,13 +1897,13 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
     // cycle expected to be the last (in tolerance mode: the one the
     // contraction of the last cycle predicts to come within 4 rtol; a cycle
     // that takes it and is not the last costs one more read of d and w).
-    const bool want_epi = P->epi_d && order == 0 && (!blocks || 2 * block_sweep_blocks(P, 0) <= kMaxPartials);
+    const bool want_epi = P->epi_d && order == 0;
     P->epi_fused = false;
     double rel_prev = 1.0;
     bool epi_next = false;
     // In register blocks the residual norm of an iterate comes with the next
     // cycle's first sweeps, as on cubic float64 plans (see solve()).
-    const bool free_norm = blocks && !fixed && block_sweep_blocks(P, 0) <= kMaxPartials;
+    const bool free_norm = blocks && !fixed && block_sweep_blocks(P, 0) <= P->npartial;
     if (status == DMGS_OK && (fixed || r0 > 0.0)) {
         for (cycles = 1; !(fixed && nfix == 0); cycles++) {
             bool done = false;
@@ -2745,7 +2756,8 @@ int grid_plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     if (P->tail_level >= 0 && st == DMGS_OK)
         st = dalloc(P, &P->ctail, unknowns(P->lev[P->tail_level]) * unknowns(P->lev[P->tail_level]));
     if (st == DMGS_OK) st = dalloc(P, &P->scratch64, P->lev[0].nv);
-    if (st == DMGS_OK) st = dalloc(P, &P->partial, kMaxPartials);
+    P->npartial = partial_entries(o, P->arena != nullptr);
+    if (st == DMGS_OK) st = dalloc(P, &P->partial, P->npartial);
     if (st == DMGS_OK) st = dalloc(P, &P->cinv, kGridCoarseMax * kGridCoarseMax);
     if (st == DMGS_OK) st = clear_flags(P, zst);
     if (P->arena) {

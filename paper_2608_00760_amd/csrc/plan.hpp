@@ -119,7 +119,8 @@ struct dmgs_plan_s {
     int cfg_2d_chunk = 0;          // ... rows per chunk (0: chosen from the grid size)
     int small32 = -1, small64 = -1;   // first level of the single-workgroup coarse kernel
     int small2 = -1;                  // ... of two-dimensional plans
-    double* partial = nullptr;     // first-stage reduction partials
+    double* partial = nullptr;     // first-stage reduction partials ...
+    int64_t npartial = dmgs::kMaxPartials;   // ... and their count
     double* cinv = nullptr;        // inverse of the coarsest operator (kCoarseMax^2 entries)
     double* ctail = nullptr;       // matrix of the cycle from level tail_level down, if any
     int tail_level = -1;
