@@ -285,15 +285,19 @@ int64_t tail_entries(const dmgs_options* o) {
     return m * m;
 }
 
-// Entries of the reductions' partials.  The block passes over a general grid's
-// finest level leave one sum a tile (the norm) or two (the likelihood's
-// epilogue, which arena plans never take: they keep the other reductions'
-// count, and past that many tiles the norm's own pass).
+// Most 8^3 tiles of a general grid's finest level whose residual norm comes
+// with the next cycle's first sweeps.  The norm's own pass and its wait are
+// then saved in every cycle, for pre-smoothing and coarse levels once more at
+// the end of a solve.  Likelihood, ms, with and without: 160x128x64 (2560
+// tiles) 10.2 / 10.4, 192x96x96 (3456) 10.31 / 10.44, 256x128x64 (4096) 17.35
+// / 17.5, 192x128x96 (4608) 14.39 / 14.35, 192x128x128 (6144) 17.76 / 17.66,
+// 256x128x128 (8192) 22.1 / 21.8.
+constexpr int64_t kGridNormTiles = 4096;
+
+// Entries of the reductions' partials (arena plans keep their size, and with
+// it the norm's own pass from kMaxPartials tiles on).
 int64_t partial_entries(const dmgs_options* o, bool arena) {
-    if (arena || !general_grid(o)) return kMaxPartials;
-    int64_t tiles = 1;
-    for (int a = 0; a < 3; a++) tiles *= Block3Shape<kB3Sweep, false>::tiles(o->n[a]);
-    return std::max<int64_t>(kMaxPartials, 2 * tiles);
+    return general_grid(o) && !arena ? kGridNormTiles : kMaxPartials;
 }
 
 // arena: without the coarse cycle's matrix and the second flag word (at most
@@ -1897,7 +1901,11 @@ int solve_grid(dmgs_plan P, const double* b, double* x, double bc, int order, dm
     // cycle expected to be the last (in tolerance mode: the one the
     // contraction of the last cycle predicts to come within 4 rtol; a cycle
     // that takes it and is not the last costs one more read of d and w).
-    const bool want_epi = P->epi_d && order == 0;
+    // Block passes take it up to one round of workgroups; from there on their
+    // strided reads of d, w and mua cost more than the pass saved (64x32x32,
+    // 256 tiles: 1.950 / 1.942 ms with and without, 96x48x48 3.012 / 2.999,
+    // 128x64x64 4.170 / 4.135, 256x128x128 22.1 / 21.8).
+    const bool want_epi = P->epi_d && order == 0 && (!blocks || block_sweep_blocks(P, 0) <= P->ncu);
     P->epi_fused = false;
     double rel_prev = 1.0;
     bool epi_next = false;
