@@ -182,6 +182,9 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options *opt);
  *   DMGS_2D_DEFECT (1)          ... the last pre-smoothing pass writes the defect
  *   DMGS_2D_CHUNK (0)           ... rows per chunk of the two-sweep passes (0: from the grid size)
  *   DMGS_2D_SMALL_MAX (64)      ... largest N of the single-workgroup coarse kernel
+ *   DMGS_TAIL_SPINS (2^22)      looks at the count of finished workgroups that the coarse kernel's
+ *                               workgroup takes before it gives up waiting for those of its launch
+ *                               (its result is then NaN, and the plan's from there on)
  *   DMGS_EPI_FUSE (1)           dmgs_likelihood_grad computes its epilogue in the
  *                               forward solve's last refinement step (0: separate pass)
  *   DMGS_PAD (1)                refinement plans pad the rows of the finest level's

@@ -300,8 +300,11 @@ int64_t partial_entries(const dmgs_options* o, bool arena) {
     return general_grid(o) && !arena ? kGridNormTiles : kMaxPartials;
 }
 
-// arena: without the coarse cycle's matrix and the second flag word (at most
-// 33 KB), which the slack of an arena plan holds.
+// Words of dflag.
+constexpr int kFlags = 3;
+
+// arena: without the coarse cycle's matrix and all but the first flag word (at
+// most 33 KB), which the slack of an arena plan holds.
 size_t footprint(const dmgs_options* o, bool arena = false) {
     Sizes s = sizes_for(o);
     bool ir = o->precision == DMGS_FP32_IN_FP64;
@@ -314,7 +317,7 @@ size_t footprint(const dmgs_options* o, bool arena = false) {
             b += (2 + (k > 0 ? 2 : 0) + (k < s.L - 1 ? 1 : 0)) * s.nv[k] * sizeof(double);
         b += s.nv[0] * sizeof(double);
         b += partial_entries(o, arena) * sizeof(double) + kGridCoarseMax * kGridCoarseMax * sizeof(double) +
-             4 * sizeof(double) + (arena ? 1 : 2) * sizeof(int);
+             4 * sizeof(double) + (arena ? 1 : kFlags) * sizeof(int);
         return b + (arena ? 0 : tail_entries(o) * sizeof(double));
     }
     const int py0 = fine_row_pitch(o, read_knobs(o), s.L);
@@ -329,7 +332,7 @@ size_t footprint(const dmgs_options* o, bool arena = false) {
     }
     b += (ir ? 2 : 1) * s.nv[0] * sizeof(double);                     // scratch64 (+ xalt64)
     b += kMaxPartials * sizeof(double) + kCoarseMax * kCoarseMax * sizeof(double) + 4 * sizeof(double) +
-         (arena ? 1 : 2) * sizeof(int);
+         (arena ? 1 : kFlags) * sizeof(int);
     return b + (arena ? 0 : tail_entries(o) * sizeof(double));
 }
 
@@ -814,7 +817,7 @@ int smooth_pass2(dmgs_plan P, int k, const T* u_in, T* u_out, const T* q, int or
         if (norm_slot >= 0) {
             a.partial = P->partial;
             a.norm = norm_dst(P) + norm_slot;
-            a.done = reinterpret_cast<unsigned*>(P->dflag + 1);
+            a.done = reinterpret_cast<unsigned*>(P->dflag + 2);
             TRY(harmonic(P) ? (launch_sweep2<T, kSweep2TY, kSweep2TZ64, true, false, true>(P, a, l.N, mode, st))
                             : (launch_sweep2<T, kSweep2TY, kSweep2TZ64, false, false, true>(P, a, l.N, mode, st)));
         } else {
@@ -1038,6 +1041,7 @@ int launch_block_tail(dmgs_plan P, int k, const Block3Args<T>& b, unsigned nb, h
     TRY((small_args<T, HARM>(P, k + 1, b.qc, Typed<T>::u(P->lev[k + 1]), b.order, a.s)));
     a.done = reinterpret_cast<unsigned*>(P->dflag + 1);
     a.nb = (int)nb;
+    a.spins = P->cfg_tail_spins;
     const void* grp = nullptr;
     if constexpr (sizeof(T) == 4) grp = (const void*)k_block_tail_grp<T, MODE, HARM>;
     return launch_rec(P, (const void*)k_block_tail<T, MODE, HARM, GEN>, grp, nb + 1, block_tail_threads<MODE, GEN>(),
@@ -1123,7 +1127,7 @@ int block_launch(dmgs_plan P, int k, int mode, const T* u_in, T* u_out, const T*
     if (parts) {
         a.partial = P->partial;
         a.norm = norm_dst(P) + norm_slot;
-        if (parts <= kSumArrivedMax) a.done = reinterpret_cast<unsigned*>(P->dflag + 1);
+        if (parts <= kSumArrivedMax) a.done = reinterpret_cast<unsigned*>(P->dflag + 2);
     }
     a.order = order;
     const bool h = harmonic(P);
@@ -2665,7 +2669,7 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options* o) {
         else b += ((k > 0 ? 3 : 1) + (o->ndim == 2 && k < s.L - 1 ? 1 : 0)) * s.nv[k] * sizeof(double);
     }
     b += (ir ? 2 : 1) * s.nv[0] * sizeof(double);
-    b += kMaxPartials * sizeof(double) + 4 * sizeof(double) + 2 * sizeof(int);
+    b += kMaxPartials * sizeof(double) + 4 * sizeof(double) + kFlags * sizeof(int);
     return footprint(o) + b;
 }
 
@@ -2718,14 +2722,17 @@ int kernel_attributes(int device) {
     return DMGS_OK;
 }
 
-// The validation flag and the count of finished workgroups, both 0.
+// The validation flag and the counts of finished workgroups, all 0, and the
+// bound of the wait for one of them.
 int clear_flags(dmgs_plan P, hipStream_t zst) {
-    TRY(dalloc(P, &P->dflag, 2));
+    P->cfg_tail_spins = kTailSpins;
+    if (const char* e = std::getenv("DMGS_TAIL_SPINS")) P->cfg_tail_spins = (unsigned)std::max(0, std::atoi(e));
+    TRY(dalloc(P, &P->dflag, kFlags));
     if (P->arena) {
-        hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(64), 0, zst, P->dflag, (int64_t)2, 0);
+        hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(64), 0, zst, P->dflag, (int64_t)kFlags, 0);
         LAUNCHCHK();
     } else {
-        HIPCHK(hipMemset(P->dflag, 0, 2 * sizeof(int)));
+        HIPCHK(hipMemset(P->dflag, 0, kFlags * sizeof(int)));
     }
     return DMGS_OK;
 }

@@ -118,21 +118,39 @@ __device__ __forceinline__ void small_wave_sync() {
 //   kSmallTail   the same as the last workgroup of the launch that restricts
 //                to a.q: loads the coefficients first, then waits for the
 //                count of finished workgroups at `done` to reach `need`
+//                (small_wait; when that gives up the result is NaN)
 //   kSmallCols   workgroup j solves for unit vector j of the first level's
 //                unknowns and writes column j of the cycle's matrix (m x m,
 //                row-major) to `mat`
 enum SmallMode { kSmallPlain = 0, kSmallTail = 1, kSmallCols = 2 };
 
-// One wait per launch, by its last workgroup, for the others of the same
-// launch, which were dispatched before it and wait for nothing: it ends when
-// they do.  The count is back at 0 when the launch ends.
-__device__ __forceinline__ void small_wait(unsigned* done, unsigned need) {
+// The wait of a launch's last workgroup (grouped: of each member's) for the
+// `need` workgroups before it, which wait for nothing.  An XCD takes a launch's
+// workgroups in order, so on the waiter's own XCD they were dispatched before
+// it, and elsewhere they wait at most for CUs: those of work that ends, or of
+// other waiters.  A launch has at most kGroupMax waiters, one a CU; only if
+// waiters held every CU of two XCDs (64) could launches hold each other up.
+// So the wait is bounded: after `spins` looks (seconds, where the others take
+// microseconds) it marks the count, so that the plan's later launches do not
+// wait either, and returns false; the result is then NaN, which tolerance
+// solves report as a non-finite residual.  Otherwise the count is back at 0
+// when the launch ends.
+constexpr unsigned kTailSpins = 1u << 22, kTailGaveUp = 1u << 31;
+__device__ __forceinline__ bool small_wait(unsigned* done, unsigned need, unsigned spins) {
+    __shared__ bool met;
     if (threadIdx.x == 0) {
-        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) __builtin_amdgcn_s_sleep(1);
+        unsigned seen = 0;   // need, or kTailGaveUp and more
+        for (unsigned i = 0; i < spins && seen < need; i++) {
+            if (i > 0) __builtin_amdgcn_s_sleep(1);
+            seen = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        met = seen == need;
+        if (met) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else __hip_atomic_fetch_or(done, kTailGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
+    return met;
 }
 // ... and what the other workgroups do once their stores are issued: the
 // restricted values are stored past the caches (block3_body with COHERENT),
@@ -145,7 +163,7 @@ __device__ __forceinline__ void small_arrive(unsigned* done) {
 
 template <class T, bool HARM, int MODE, int NT = kSmallThreads>
 __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a, unsigned* done = nullptr, unsigned need = 0,
-                                                  double* mat = nullptr) {
+                                                  unsigned spins = 0, double* mat = nullptr) {
     extern __shared__ __align__(16) unsigned char block_smem[];
     T* const base = reinterpret_cast<T*>(block_smem);
     const int tid = threadIdx.x, L = a.nlev;
@@ -168,11 +186,11 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a, unsigne
     const int cx = a.lev[L - 1].nc[0] - 1, cy = a.lev[L - 1].nc[1] - 1, cz = a.lev[L - 1].nc[2] - 1;
     const int m = cx * cy * cz;
     if (MODE != kSmallCols && L == 1) {   // nothing to smooth: u = A^-1 q straight from memory
-        if (MODE == kSmallTail) small_wait(done, need);
+        const bool met = MODE != kSmallTail || small_wait(done, need, spins);
         if (tid < m) {
             const int n1 = cy + 2, n2 = cz + 2;
             auto gid = [&](int c) { return ((1 + c / (cy * cz)) * n1 + 1 + (c / cz) % cy) * n2 + 1 + c % cz; };
-            double acc = 0.0;
+            double acc = met ? 0.0 : __builtin_nan("");
             for (int c = 0; c < m; c++) acc += a.cinv[a.ctrans ? c * m + tid : tid * m + c] *
                        (double)__hip_atomic_load(a.q + gid(c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             a.u[gid(tid)] = (T)acc;
@@ -243,10 +261,12 @@ __device__ __forceinline__ void small_vcycle_body(const SmallArgs<T>& a, unsigne
             if ((o & B3::bit(ax)) && edge[ax]) base[idx + B3::outer(ax, o)] = T(0);
 
     if (MODE == kSmallTail) {
-        small_wait(done, need);
+        const bool met = small_wait(done, need, spins);
 #pragma unroll
-        for (int o = 0; o < 8; o++)
+        for (int o = 0; o < 8; o++) {
             P.q[o] = act && ml == 0 ? __hip_atomic_load(a.q + vert(o), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : T(0);
+            P.q[o] = met ? P.q[o] : T(__builtin_nan(""));
+        }
     } else if (MODE == kSmallCols) {
         // unknowns of the first level in x, y, z order
 #pragma unroll
@@ -372,7 +392,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_vcycle(SmallArgs<T> a) 
 // below it took 40 % of the chain of steps for 28 unknowns.
 template <class T, bool HARM>
 __global__ __launch_bounds__(kSmallThreads) void k_small_cols(SmallArgs<T> a, double* mat) {
-    small_vcycle_body<T, HARM, kSmallCols>(a, nullptr, 0, mat);
+    small_vcycle_body<T, HARM, kSmallCols>(a, nullptr, 0, 0, mat);
 }
 
 // Grouped form: one workgroup per member.
@@ -393,6 +413,7 @@ struct BlockTailArgs {
     SmallArgs<T> s;
     unsigned* done;   // 0 between launches
     int nb;           // workgroups of the block pass
+    unsigned spins;   // bound of the last workgroup's wait
 };
 
 template <int MODE, bool GEN>
@@ -410,7 +431,7 @@ __device__ __forceinline__ void block_tail_body(const BlockTailArgs<T>& a, int b
         block3_body<T, MODE, HARM, GEN, true>(a.b, bid);
         small_arrive(a.done);
     } else {
-        small_vcycle_body<T, HARM, kSmallTail, block_tail_threads<MODE, GEN>()>(a.s, a.done, (unsigned)a.nb);
+        small_vcycle_body<T, HARM, kSmallTail, block_tail_threads<MODE, GEN>()>(a.s, a.done, (unsigned)a.nb, a.spins);
     }
 }
 

@@ -125,8 +125,9 @@ struct dmgs_plan_s {
     double* ctail = nullptr;       // matrix of the cycle from level tail_level down, if any
     int tail_level = -1;
     double* hnorm = nullptr;       // pinned host memory the reductions write their norms to (4 slots)
-    int* dflag = nullptr;          // device validation flag; [1]: finished workgroups of a launch whose last one goes on: the
-                                   // coarse kernel, a norm (0 between launches)
+    int* dflag = nullptr;          // device validation flag; finished workgroups of a launch whose last one goes on
+                                   // (0 between launches), [1] with the coarse kernel, [2] with a norm
+    unsigned cfg_tail_spins = 0;   // bound of the coarse kernel's wait for the launch's other workgroups
     int* hflag = nullptr;          // pinned host mirror
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     hipEvent_t ev_norm = nullptr;  // recorded after the last norm reduction
