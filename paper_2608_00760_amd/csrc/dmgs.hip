@@ -1055,10 +1055,13 @@ int64_t block_sweep_blocks(dmgs_plan P, int k) {
     return nb;
 }
 
-// A norm's parts are added up by the launch's last workgroup while about one
+// A norm's parts are added up by a block pass's last workgroup while about one
 // round of workgroups counts itself (32^3, 64 of them: 77 us less in a solve
 // and pull-back of 1.5 ms); with more the counting itself takes longer than a
-// launch for the sum (1024: 34.5 us for 29 + 4).
+// launch for the sum (1024: 34.5 us for 29 + 4).  The marching passes, at most
+// 512 workgroups of several times the length, always do it: with the sum as a
+// launch of its own from 257 on a solve took the same (192^3, 504 of them,
+// 6.03 / 6.03 ms; 512^3, 512, 68.6 / 68.6).
 constexpr int64_t kSumArrivedMax = 256;
 
 template <class T, int MODE, bool HARM>

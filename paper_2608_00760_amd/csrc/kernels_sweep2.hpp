@@ -60,7 +60,8 @@
 // u_j from the input, and the residual is that minus u_i / w_i.  When the
 // input ended a red-black sweep whose last colour is this pass's second,
 // the second colour's residual is 0 (up to rounding), so the block sums
-// (one per workgroup, in a.partial) add up to ||q - A u||^2 of the input; the last workgroup adds them up.
+// (one per workgroup, in a.partial) add up to ||q - A u||^2 of the input; the
+// last workgroup does so (sum_arrived), whatever their number.
 #pragma once
 #include "kernels_stream.hpp"
 
