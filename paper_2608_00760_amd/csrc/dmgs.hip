@@ -2912,7 +2912,8 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
     // every work buffer starts at 0: the passes never write boundary layers
     // or row padding, and coarse corrections have homogeneous boundaries (an
     // arena keeps the last call's contents, so its buffers are cleared on the
-    // stream); the coefficient arrays' row padding is 0 as well
+    // stream); the coefficient arrays' row padding is 0 as well.  The caller's
+    // streams need not wait for the null stream, so the host does.
     for (int k = 0; k < P->L && st == DMGS_OK; k++) {
         Level& l = P->lev[k];
         void* ps[] = {l.u64, l.q64, l.t64, l.u32, l.q32, l.t32, l.r32, l.rd64, l.D32, l.mu32, l.w32};
@@ -2929,6 +2930,10 @@ int plan_init(dmgs_plan P, const dmgs_options* o, hipStream_t zst) {
                 st = DMGS_ERR_HIP;
             }
         }
+    }
+    if (st == DMGS_OK && !P->arena && hipStreamSynchronize(nullptr) != hipSuccess) {
+        (void)hipGetLastError(); set_error("stream synchronisation failed");
+        st = DMGS_ERR_HIP;
     }
     P->cfg_sweep = 0;
     P->cfg_fuse_min = kn.fuse_min;
