@@ -173,7 +173,8 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options *opt);
  *   DMGS_SWEEP2_FP64 (1)        float64 levels with a zero boundary use the two-sweep pass
  *   DMGS_SWEEP_CFG (0)          float32 one-sweep pass tiles: 0 16x64, 1 8x64, 2 16x32
  *   DMGS_FUSE_MIN (32 / 16)     smallest N of the fused passes (float32 / float64 plans)
- *   DMGS_BLOCK_MAX (64)         largest N of the register-block passes
+ *   DMGS_BLOCK_MAX (64)         largest N of the register-block passes (V(2,2) plans, both precisions;
+ *                               before the passes above)
  *   DMGS_DR_WGS (512 / 1024)    target workgroups of the defect-restriction pass (float32 / float64 plans)
  *   DMGS_2D_SWEEP2_MIN          two-dimensional plans: smallest N of the row-marching two-sweep
  *                               passes (unset: none in V(2,2) plans, whose levels run the block

@@ -201,9 +201,10 @@ struct Knobs {
 
 Knobs read_knobs(const dmgs_options* o) {
     const bool ir = o->precision == DMGS_FP32_IN_FP64;
-    // float64 plans have no block passes: their two-sweep passes reach down
-    // to the levels the small-level kernel leaves (one launch per phase
-    // instead of two)
+    // Float64 two-sweep passes reach down to the levels the coarse kernel
+    // leaves (one launch per phase instead of two); in V(2,2) plans levels of
+    // at most block_max cells run the block passes before that, so this is for
+    // other smoothing counts and for larger levels.
     Knobs k{ir ? 32 : 16, ir ? 64 : 16, 64, 2, true};
     if (const char* e = std::getenv("DMGS_FUSE_MIN")) k.fuse_min = std::max(8, std::atoi(e));
     if (const char* e = std::getenv("DMGS_SWEEP2_MIN")) k.sweep2_min = std::max(16, std::atoi(e));

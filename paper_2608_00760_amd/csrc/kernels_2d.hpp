@@ -971,7 +971,7 @@ __global__ __launch_bounds__(1024) void k2_small_vcycle(Small2Args a) {
 // Bound by latency up to 512^2 (one round of workgroups: load, four
 // half-sweeps, store) and above by the loads of the box.  Measured
 // (pre- / post-smoothing): 128^2 .. 512^2 5 us each, 1024^2 13 / 13 us, 4096^2
-// 172 / 151 us (5.1 TB/s of one read of u, q, D, mua and one write of u).
+// 172 / 151 us (3.9 / 4.4 TB/s of one read of u, q, D, mua and one write of u).
 // Holding u, q, D and mua in LDS and dividing by the diagonal in every update
 // took 14 / 17 us at 128^2 .. 512^2 and 35 / 40 us at 1024^2; the row-marching
 // passes 84 / 62 us at 2048^2 and 242 / 192 us at 4096^2 (with the separate
