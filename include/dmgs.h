@@ -187,7 +187,9 @@ size_t dmgs_forward_vjp_workspace_bytes(const dmgs_options *opt);
  *                               workgroup takes before it gives up waiting for those of its launch
  *                               (its result is then NaN, and the plan's from there on)
  *   DMGS_EPI_FUSE (1)           dmgs_likelihood_grad computes its epilogue in the
- *                               forward solve's last refinement step (0: separate pass)
+ *                               forward solve's last refinement step or pass (general
+ *                               grids: up to one round of block passes' workgroups;
+ *                               0: separate pass)
  *   DMGS_PAD (1)                refinement plans pad the rows of the finest level's
  *                               float32 arrays to a multiple of four elements when
  *                               every pass there takes a pitch (even smoothing

@@ -151,6 +151,10 @@ struct Block3 {
 //   kB3Defect   the restricted defect of u_in, whose last half-sweep updated
 //               the second colour
 //   kB3Post     u_in plus the trilinear correction, two sweeps, u
+//   kB3PostEpi  kB3Post on a general grid of at most one round of workgroups,
+//               with the likelihood epilogue of the result: rhobar = mua w
+//               (mua u - d) (0 on the boundary) and per-workgroup sums of
+//               w (mua u - d)^2 and of w > 0
 // Every block of the box is updated in every half-sweep; a vertex j rings
 // inside the box then has the sequential sweeps' value after half-sweep j.
 // What is formed nearer to the edge, from neighbours the box does not hold,
@@ -173,9 +177,6 @@ struct Block3 {
 // 9.6 / 8.8 us); float64 48^3 9.3 / 7.4 us, 24^3 7.7 / 7.0 us (marching passes
 // with the separate restriction 24 / 21 and 22 / 20 us); the paper's
 // 128 x 64 x 64 grid 29 + 10 / 27 us (one operation per launch: 47 / 44 us).
-//   kB3PostEpi  kB3Post on a general grid, with the likelihood epilogue of
-//               the result: rhobar = mua w (mua u - d) (0 on the boundary)
-//               and per-workgroup sums of w (mua u - d)^2 and of w > 0
 enum Block3Mode { kB3PreZero = 0, kB3Pre = 1, kB3Sweep = 2, kB3Defect = 3, kB3Post = 4, kB3PostEpi = 5, kB3Zero = 6 };
 
 template <class T>
